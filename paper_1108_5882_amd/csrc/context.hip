@@ -607,6 +607,12 @@ hipError_t stage_rows(void *dst, size_t dst_pitch, const void *src, size_t src_p
         return e != hipSuccess ? e : hipStreamSynchronize(stream);
     }
     if (kind != hipMemcpyHostToDevice) {
+        // one pass; rows of an odd number of 8-byte units (a layout of 1 or 3 FP32
+        // waves) and sources that are not 8-byte aligned take the pitched copy
+        if (dst_pitch % 16 == 0 && width % 8 == 0 && src_pitch % 8 == 0 && reinterpret_cast<uintptr_t>(src) % 8 == 0) {
+            e = launch_pack_rows(dst, dst_pitch, src, src_pitch, width, n, stream);
+            return e != hipSuccess ? e : hipStreamSynchronize(stream);
+        }
         if (dst_pitch > width && (e = hipMemsetAsync(d, 0, dst_pitch * n, stream)) != hipSuccess) return e;
         e = hipMemcpy2DAsync(d, dst_pitch, sp, src_pitch, width, n, kind, stream);
         return e != hipSuccess ? e : hipStreamSynchronize(stream);

@@ -229,6 +229,11 @@ hipError_t launch_lbfgs(const MultiFit *fits, int k_all, const double *out, int6
 hipError_t stage_rows(void *dst, size_t dst_pitch, const void *src, size_t src_pitch, size_t width, size_t n,
                       hipMemcpyKind kind, hipStream_t stream);
 
+// The device-to-device form of stage_rows in one kernel, without a wait:
+// dst_pitch a multiple of 16 bytes, src, src_pitch and width of 8.
+hipError_t launch_pack_rows(void *dst, size_t dst_pitch, const void *src, size_t src_pitch, size_t width, size_t n,
+                            hipStream_t stream);
+
 // Sets *bad (device word, zeroed by the caller) to 1 if a row of the sample
 // (n rows of ld complex in the precision) holds a nonzero value in columns
 // [k, ld).  Nothing is launched when ld == k.
