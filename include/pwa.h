@@ -464,7 +464,9 @@ int64_t pwa_mlp_param_count(int32_t in, int32_t hidden);
 
 /* Create a network on `device` (parameters zero; set them with
  * pwa_mlp_set_params).  in 1..128, hidden 1..4096; max_batch 1..65536 rows
- * bounds the training batch and the rows one inference pass holds.
+ * bounds the training batch and, for networks that are not inferred in one
+ * launch (hidden other than 256, or more than 64 inputs), the rows one
+ * inference pass holds.
  * `stream`: hipStream_t or NULL (owned). */
 pwa_status pwa_mlp_create(pwa_mlp **out, int device, int32_t in, int32_t hidden, int32_t max_batch,
                           void *stream);

@@ -297,6 +297,10 @@ hipError_t mlp_targets(const double *nll, int64_t n, float *t, hipStream_t s);
 // too when hist is set) and the gradient of the summed squared error into m.G.
 hipError_t mlp_pass(const MlpBuffers &m, int B, const float *Xb, const float *tb, float *y, bool train, float *hist,
                     hipStream_t s);
+// Inference of n rows in one launch (mlp_predict.hip) where mlp_predict_ok: the
+// outputs of mlp_pass, bit for bit, without its activation buffers.
+bool mlp_predict_ok(const MlpBuffers &m);
+hipError_t mlp_predict(const MlpBuffers &m, int cu_count, const float *X, int64_t n, float *y, hipStream_t s);
 hipError_t mlp_scale(const float *x, int64_t n, float scale, float *out, hipStream_t s);
 // Fused training pass (mlp_fused.hip), hidden width 256 and in <= 128 only: per
 // slice of 16 rows (X rows perm[*m.batch B + r] when perm is set, else rows

@@ -20,6 +20,7 @@ struct pwa_mlp {
     int device = 0;
     hipStream_t stream = nullptr;
     bool own_stream = false;
+    int cu_count = 1;
     MlpBuffers m{};
     std::vector<void *> allocs;
     float *tk_key[2] = {nullptr, nullptr};
@@ -185,7 +186,8 @@ pwa_status pwa_mlp_create(pwa_mlp **out, int device, int32_t in, int32_t hidden,
             return st;
         }
     }
-    hipError_t e = hipMemsetAsync(b.P, 0, sizeof(float) * b.nparams, m->stream);
+    hipError_t e = hipDeviceGetAttribute(&m->cu_count, hipDeviceAttributeMultiprocessorCount, device);
+    if (e == hipSuccess) e = hipMemsetAsync(b.P, 0, sizeof(float) * b.nparams, m->stream);
     if (e == hipSuccess) e = hipMemsetAsync(b.M1, 0, sizeof(float) * b.nparams, m->stream);
     if (e == hipSuccess) e = hipMemsetAsync(b.M2, 0, sizeof(float) * b.nparams, m->stream);
     if (e == hipSuccess) e = hipMemsetAsync(ints, 0, sizeof(int) * 4, m->stream);
@@ -259,7 +261,8 @@ pwa_status pwa_mlp_predict(pwa_mlp *m, const float *X, int64_t n, float *y) {
     if (!m || n < 0 || (n > 0 && (!X || !y))) return lfail(m, PWA_E_INVAL, "bad arguments");
     Guard g(m->device);
     const MlpBuffers &b = m->m;
-    for (int64_t off = 0; off < n; off += b.max_batch) {
+    if (mlp_predict_ok(b)) L_HIP(m, mlp_predict(b, m->cu_count, X, n, y, m->stream), "inference launch");
+    for (int64_t off = mlp_predict_ok(b) ? n : 0; off < n; off += b.max_batch) {
         const int B = (int)std::min<int64_t>(b.max_batch, n - off);
         L_HIP(m, mlp_pass(b, B, X + off * b.in, nullptr, y + off, false, nullptr, m->stream), "forward launch");
     }
