@@ -329,6 +329,6 @@ hipError_t mlp_set_int(int *p, int v, hipStream_t s);
 // Indices of the k smallest keys (ties by index; NaN counts as +inf), ascending.
 int topk_chunk();
 size_t topk_scratch(int64_t n, int k);
-hipError_t mlp_topk(const float *keys, int64_t n, int k, float *sk[2], int *si[2], int *out, hipStream_t s);
+hipError_t mlp_topk(const float *keys, int64_t n, int k, unsigned long long *sk[2], int *out, hipStream_t s);
 
 }  // namespace pwa

@@ -330,23 +330,41 @@ __global__ void gather_kernel(const float *X, const float *t, const int *perm, c
     }
 }
 
-// Features: V^ = V e^{-i arg V_0} / |V|, interleaved (re, im), FP32.
-__global__ void features_kernel(const double *V, int64_t n, int k, float *X) {
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
-        const double *v = V + r * 2 * k;
+// Features: V^ = V e^{-i arg V_0} / |V|, interleaved (re, im), FP32.  A block
+// stages kFeatRows rows in LDS with coalesced loads, one thread per row forms
+// the norm (its terms in order) and the phase, and all threads write the
+// features in order.  Bound by HBM (24 bytes per real of V).  10^5 rows of 16
+// waves with one thread walking each row in memory 30 us, so 11 us.
+constexpr int kFeatRows = 32;
+__global__ __launch_bounds__(256) void features_kernel(const double *V, int64_t n, int k, float *X) {
+    extern __shared__ double feat[];                   // rows of 2k doubles, an odd number apart
+    __shared__ double s_m0[kFeatRows], s_cr[kFeatRows], s_ci[kFeatRows], s_inv[kFeatRows];
+    const int tid = threadIdx.x, w = 2 * k, stride = w + 1;
+    const int64_t r0 = (int64_t)blockIdx.x * kFeatRows;
+    const int rows = (int)(n - r0 < kFeatRows ? n - r0 : kFeatRows);
+    const double *src = V + r0 * w;
+    for (int i = tid; i < rows * w; i += 256) feat[i / w * stride + i % w] = src[i];
+    __syncthreads();
+    if (tid < rows) {
+        const double *v = feat + tid * stride;
         double nrm = 0.0;
-        for (int a = 0; a < 2 * k; ++a) nrm += v[a] * v[a];
+        for (int a = 0; a < w; ++a) nrm += v[a] * v[a];
         nrm = sqrt(nrm);
         const double m0 = hypot(v[0], v[1]);
-        const double cr = m0 > 0.0 ? v[0] / m0 : 1.0, ci = m0 > 0.0 ? -v[1] / m0 : 0.0;   // e^{-i arg V_0}
-        const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
-        X[r * 2 * k] = (float)(m0 * inv);                  // V_0 e^{-i arg V_0} = |V_0|: real
-        X[r * 2 * k + 1] = 0.f;
-        for (int a = 1; a < k; ++a) {
-            const double re = v[2 * a], im = v[2 * a + 1];
-            X[r * 2 * k + 2 * a] = (float)((re * cr - im * ci) * inv);
-            X[r * 2 * k + 2 * a + 1] = (float)((re * ci + im * cr) * inv);
-        }
+        s_m0[tid] = m0;
+        s_cr[tid] = m0 > 0.0 ? v[0] / m0 : 1.0;        // e^{-i arg V_0}
+        s_ci[tid] = m0 > 0.0 ? -v[1] / m0 : 0.0;
+        s_inv[tid] = nrm > 0.0 ? 1.0 / nrm : 0.0;
+    }
+    __syncthreads();
+    float *dst = X + r0 * w;
+    for (int i = tid; i < rows * k; i += 256) {
+        const int r = i / k, a = i % k;
+        const double cr = s_cr[r], ci = s_ci[r], inv = s_inv[r];
+        const double re = feat[r * stride + 2 * a], im = feat[r * stride + 2 * a + 1];
+        // V_0 e^{-i arg V_0} = |V_0|: real
+        dst[2 * i] = a == 0 ? (float)(s_m0[r] * inv) : (float)((re * cr - im * ci) * inv);
+        dst[2 * i + 1] = a == 0 ? 0.f : (float)((re * ci + im * cr) * inv);
     }
 }
 
@@ -377,25 +395,170 @@ __global__ void targets_kernel(const double *nll, int64_t n, float *t) {
         t[i] = !any ? 0.f : isfinite(nll[i]) ? (float)log1p(nll[i] - lo) : (float)cap;
 }
 
-// Top-k smallest (ties by index, NaN as +inf): each block sorts a chunk of
-// kChunk (key, index) pairs in LDS (bitonic) and keeps its k best; rounds
-// repeat on the survivors until one chunk is left.
-constexpr int kChunk = 4096;
+// Top-k smallest (ties by index, NaN as +inf).  A key and its index become one
+// unsigned 64-bit number whose order is theirs; lists of these are merged until
+// one is left.
+typedef unsigned long long u64;
+constexpr int kChunk = 4096;                    // keys a block takes at first
+constexpr u64 kNone = 0xff8000007fffffffull;    // after every key: +inf with the largest index
 
-__device__ __forceinline__ bool less_kv(float ka, int ia, float kb, int ib) {
-    return ka < kb || (ka == kb && ia < ib);
+__device__ __forceinline__ u64 order_of(float key, int index) {
+    if (isnan(key)) key = INFINITY;
+    if (key == 0.f) key = 0.f;                  // -0 and +0 tie
+    const unsigned b = __float_as_uint(key);
+    return ((u64)(b & 0x80000000u ? ~b : b | 0x80000000u) << 32) | (unsigned)index;
 }
 
-__global__ __launch_bounds__(1024) void topk_chunk_kernel(const float *keys, const int *ids, int n, int k,
-                                                          float *ok, int *oi) {
-    __shared__ float key[kChunk];
-    __shared__ int idx[kChunk];
-    const int base = blockIdx.x * kChunk;
+// value of lane ^ M
+template <int M>
+__device__ __forceinline__ unsigned lane_xor(unsigned x) {
+    if constexpr (M == 1) return __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, true);     // quad_perm [1,0,3,2]
+    if constexpr (M == 2) return __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, true);     // quad_perm [2,3,0,1]
+    if constexpr (M == 4)                                                                     // lane ^ 3, then ^ 7
+        return __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, x, 0x1B, 0xF, 0xF, true), 0x141, 0xF, 0xF,
+                                           true);
+    if constexpr (M == 8) return __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, true);    // row_ror 8
+    if constexpr (M == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return (threadIdx.x & 16) ? r[0] : r[1];
+    }
+    if constexpr (M == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return (threadIdx.x & 32) ? r[0] : r[1];
+    }
+}
+template <int M>
+__device__ __forceinline__ u64 lane_xor64(u64 x) {
+    return ((u64)lane_xor<M>((unsigned)(x >> 32)) << 32) | lane_xor<M>((unsigned)x);
+}
+
+// A wave's list: 64 E numbers, number i = E lane + r in register r of a lane.
+// One compare-exchange step at distance S within ascending and descending runs
+// of `size` (size 0: the whole list ascends).
+template <int E, int S>
+__device__ __forceinline__ void exchange(u64 (&v)[E], int size, int lane) {
+    if constexpr (S < E) {
+#pragma unroll
+        for (int r = 0; r < E; ++r)
+            if ((r & S) == 0) {
+                const bool up = ((E * lane + r) & size) == 0;
+                const u64 a = v[r], b = v[r + S];
+                const bool sw = up == (b < a);
+                v[r] = sw ? b : a;
+                v[r + S] = sw ? a : b;
+            }
+    } else {
+        // lane L's partner differs in one lane bit; the lower lane of an ascending
+        // pair keeps the smaller number
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+            const bool small = ((E * lane & S) == 0) == ((E * lane & size) == 0);
+            const u64 a = v[r], b = lane_xor64<S / E>(a);
+            v[r] = small == (b < a) ? b : a;
+        }
+    }
+}
+template <int E, int S>
+__device__ __forceinline__ void cleaner(u64 (&v)[E], int size, int lane) {
+    exchange<E, S>(v, size, lane);
+    if constexpr (S > 1) cleaner<E, S / 2>(v, size, lane);
+}
+template <int E, int SIZE>
+__device__ __forceinline__ void sort_list(u64 (&v)[E], int lane) {
+    if constexpr (SIZE > 2) sort_list<E, SIZE / 2>(v, lane);
+    cleaner<E, SIZE / 2>(v, SIZE == 64 * E ? 0 : SIZE, lane);
+}
+// v := the 64 E smallest of v and another ascending list (o: it in reverse order)
+template <int E>
+__device__ __forceinline__ void merge_list(u64 (&v)[E], const u64 (&o)[E], int lane) {
+#pragma unroll
+    for (int r = 0; r < E; ++r) v[r] = o[r] < v[r] ? o[r] : v[r];
+    cleaner<E, 32 * E>(v, 0, lane);             // a bitonic list
+}
+
+// Block b keeps the 64 E smallest numbers of its share, ascending, in
+// lists[b * 64 E ..], or their first k indices in out when there is one block.
+// First round (src null): kChunk keys, each wave sorting 64 E of them at a time.
+// Later rounds: lists_per_block ascending lists of src.  Waves merge what they
+// take, then pairs of waves merge through LDS.
+//
+// Bound: instruction issue of few waves.  10^5 keys, k = 256: launches of
+// 13 and 8 us, where three rounds of a bitonic sort of 4096 numbers in LDS (78
+// steps with a barrier each) took 88 us each.
+template <int E>
+__global__ __launch_bounds__(1024) void topk_merge_kernel(const float *keys, const u64 *src, int64_t n,
+                                                          int lists_per_block, int k, u64 *lists, int *out) {
+    constexpr int L = 64 * E, W = 16;
+    __shared__ u64 tile[W / 2][L];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    u64 v[E], o[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r) v[r] = kNone;
+    if (!src) {
+        const int64_t base = (int64_t)blockIdx.x * kChunk;
+        for (int c = wave; c < kChunk / L; c += W) {
+#pragma unroll
+            for (int r = 0; r < E; ++r) {
+                const int64_t g = base + (int64_t)c * L + 64 * r + lane;    // any order: it is sorted next
+                o[r] = g < n ? order_of(keys[g], (int)g) : kNone;
+            }
+            sort_list<E, L>(o, lane);
+            if (c == wave) {
+#pragma unroll
+                for (int r = 0; r < E; ++r) v[r] = o[r];
+            }
+        }
+    } else {
+        const int64_t l0 = (int64_t)blockIdx.x * lists_per_block;
+        const int64_t l1 = l0 + lists_per_block < n ? l0 + lists_per_block : n;
+        bool first = true;
+        for (int64_t l = l0 + wave; l < l1; l += W) {
+            if (first) {
+#pragma unroll
+                for (int r = 0; r < E; ++r) v[r] = src[l * L + E * lane + r];
+            } else {
+#pragma unroll
+                for (int r = 0; r < E; ++r) o[r] = src[l * L + L - 1 - (E * lane + r)];
+                merge_list<E>(v, o, lane);
+            }
+            first = false;
+        }
+    }
+    for (int half = W / 2; half >= 1; half >>= 1) {
+        __syncthreads();
+        if (wave >= half && wave < 2 * half) {
+#pragma unroll
+            for (int r = 0; r < E; ++r) tile[wave - half][L - 1 - (E * lane + r)] = v[r];
+        }
+        __syncthreads();
+        if (wave < half) {
+#pragma unroll
+            for (int r = 0; r < E; ++r) o[r] = tile[wave][E * lane + r];
+            merge_list<E>(v, o, lane);
+        }
+    }
+    if (wave != 0) return;
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+        const int i = E * lane + r;
+        if (out) {
+            if (i < k) out[i] = (int)(unsigned)v[r];
+        } else {
+            lists[(int64_t)blockIdx.x * L + i] = v[r];
+        }
+    }
+}
+
+// More than 512 kept: each block sorts kChunk numbers in LDS (bitonic) and keeps
+// the k smallest; rounds repeat on the survivors until one block is left, which
+// writes their indices to out.
+__global__ __launch_bounds__(1024) void topk_chunk_kernel(const float *keys, const u64 *src, int64_t n, int k,
+                                                          u64 *kept, int *out) {
+    __shared__ u64 v[kChunk];
+    const int64_t base = (int64_t)blockIdx.x * kChunk;
     for (int i = threadIdx.x; i < kChunk; i += blockDim.x) {
-        const int g = base + i;
-        const float v = g < n ? keys[g] : INFINITY;
-        key[i] = isnan(v) ? INFINITY : v;
-        idx[i] = g < n ? (ids ? ids[g] : g) : 0x7fffffff;
+        const int64_t g = base + i;
+        v[i] = g >= n ? kNone : src ? src[g] : order_of(keys[g], (int)g);
     }
     __syncthreads();
     for (int size = 2; size <= kChunk; size <<= 1)
@@ -403,24 +566,20 @@ __global__ __launch_bounds__(1024) void topk_chunk_kernel(const float *keys, con
             for (int i = threadIdx.x; i < kChunk; i += blockDim.x) {
                 const int j = i ^ stride;
                 if (j > i) {
-                    const bool up = (i & size) == 0;
-                    const bool sw = up ? less_kv(key[j], idx[j], key[i], idx[i])
-                                       : less_kv(key[i], idx[i], key[j], idx[j]);
-                    if (sw) {
-                        const float tk = key[i];
-                        key[i] = key[j];
-                        key[j] = tk;
-                        const int ti = idx[i];
-                        idx[i] = idx[j];
-                        idx[j] = ti;
+                    const u64 a = v[i], b = v[j];
+                    if (((i & size) == 0) == (b < a)) {
+                        v[i] = b;
+                        v[j] = a;
                     }
                 }
             }
             __syncthreads();
         }
     for (int i = threadIdx.x; i < k; i += blockDim.x) {
-        ok[blockIdx.x * k + i] = key[i];
-        oi[blockIdx.x * k + i] = idx[i];
+        if (out)
+            out[i] = (int)(unsigned)v[i];
+        else
+            kept[(int64_t)blockIdx.x * k + i] = v[i];
     }
 }
 
@@ -450,8 +609,9 @@ int64_t mlp_param_count(int in, int hidden) {
 
 hipError_t mlp_features(const double *V, int64_t n, int k, float *X, hipStream_t s) {
     if (n == 0) return hipSuccess;
-    const int blocks = (int)std::min<int64_t>((n + 255) / 256, 4096);
-    hipLaunchKernelGGL(features_kernel, dim3(blocks), dim3(256), 0, s, V, n, k, X);
+    const int64_t blocks = (n + kFeatRows - 1) / kFeatRows;
+    hipLaunchKernelGGL(features_kernel, dim3((unsigned)blocks), dim3(256), sizeof(double) * kFeatRows * (2 * k + 1), s,
+                       V, n, k, X);
     return hipGetLastError();
 }
 
@@ -531,32 +691,41 @@ hipError_t mlp_set_int(int *p, int v, hipStream_t s) {
 
 int topk_chunk() { return kChunk; }
 
+// Numbers per list of the merging form (k up to 512), or per block of the other.
+static int topk_list(int k) { return k <= 256 ? 256 : k <= 512 ? 512 : k; }
+
 size_t topk_scratch(int64_t n, int k) {
     const int64_t chunks = (n + kChunk - 1) / kChunk;
-    return (size_t)std::max<int64_t>(chunks, 1) * k;
+    return (size_t)std::max<int64_t>(chunks, 1) * topk_list(k);
 }
 
-// Indices of the k smallest of n keys into out (k <= kChunk / 2); sk, si:
-// two ping-pong scratch areas of topk_scratch(n, k) pairs each.
-hipError_t mlp_topk(const float *keys, int64_t n, int k, float *sk[2], int *si[2], int *out, hipStream_t s) {
+// Indices of the k smallest of n keys into out (k <= kChunk / 2); sk: two
+// ping-pong scratch areas of topk_scratch(n, k) numbers each.
+hipError_t mlp_topk(const float *keys, int64_t n, int k, unsigned long long *sk[2], int *out, hipStream_t s) {
     if (k < 1 || k > kChunk / 2 || n < k) return hipErrorInvalidValue;
-    const float *kin = keys;
-    const int *iin = nullptr;
-    int64_t m = n;
-    int buf = 0;
-    for (;;) {
-        const int64_t chunks = (m + kChunk - 1) / kChunk;
-        hipLaunchKernelGGL(topk_chunk_kernel, dim3((unsigned)chunks), dim3(1024), 0, s, kin, iin, (int)m, k, sk[buf],
-                           si[buf]);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        kin = sk[buf];
-        iin = si[buf];
-        m = chunks * k;
-        buf ^= 1;
-        if (chunks == 1) break;
+    // lists a block of a later round merges: four per wave keep the rounds few
+    constexpr int kLists = 64;
+    const u64 *src = nullptr;
+    int64_t m = n;                              // keys, then lists (k <= 512) or numbers
+    for (int buf = 0;; buf ^= 1) {
+        const bool merge = k <= 512;
+        const int per_block = src && merge ? kLists : kChunk;
+        const int64_t blocks = (m + per_block - 1) / per_block;
+        int *last = blocks == 1 ? out : nullptr;
+        if (k <= 256)
+            hipLaunchKernelGGL(topk_merge_kernel<4>, dim3((unsigned)blocks), dim3(1024), 0, s, keys, src, m, kLists, k,
+                               sk[buf], last);
+        else if (merge)
+            hipLaunchKernelGGL(topk_merge_kernel<8>, dim3((unsigned)blocks), dim3(1024), 0, s, keys, src, m, kLists, k,
+                               sk[buf], last);
+        else
+            hipLaunchKernelGGL(topk_chunk_kernel, dim3((unsigned)blocks), dim3(1024), 0, s, keys, src, m, k, sk[buf],
+                               last);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || last) return e;
+        src = sk[buf];
+        m = merge ? blocks : blocks * k;
     }
-    return hipMemcpyAsync(out, iin, sizeof(int) * k, hipMemcpyDeviceToDevice, s);
 }
 
 }  // namespace pwa

@@ -23,8 +23,7 @@ struct pwa_mlp {
     int cu_count = 1;
     MlpBuffers m{};
     std::vector<void *> allocs;
-    float *tk_key[2] = {nullptr, nullptr};
-    int *tk_idx[2] = {nullptr, nullptr};
+    unsigned long long *tk[2] = {nullptr, nullptr};     // top-k scratch
     size_t tk_cap = 0;
     hipGraph_t graph = nullptr, graph_n = nullptr;      // one training step; kGroupSteps steps
     hipGraphExec_t exec = nullptr, exec_n = nullptr;
@@ -207,10 +206,8 @@ pwa_status pwa_mlp_destroy(pwa_mlp *m) {
     if (m->stream) (void)hipStreamSynchronize(m->stream);
     drop_graph(m);
     for (void *p : m->allocs) (void)hipFree(p);
-    for (int i = 0; i < 2; ++i) {
-        if (m->tk_key[i]) (void)hipFree(m->tk_key[i]);
-        if (m->tk_idx[i]) (void)hipFree(m->tk_idx[i]);
-    }
+    for (unsigned long long *p : m->tk)
+        if (p) (void)hipFree(p);
     if (m->own_stream && m->stream) (void)hipStreamDestroy(m->stream);
     delete m;
     return PWA_OK;
@@ -349,20 +346,15 @@ pwa_status pwa_mlp_select(pwa_mlp *m, const float *keys, int64_t n, int32_t k, i
     Guard g(m->device);
     const size_t need = topk_scratch(n, k);
     if (need > m->tk_cap) {
-        for (int i = 0; i < 2; ++i) {
-            if (m->tk_key[i]) (void)hipFree(m->tk_key[i]);
-            if (m->tk_idx[i]) (void)hipFree(m->tk_idx[i]);
-            m->tk_key[i] = nullptr;
-            m->tk_idx[i] = nullptr;
+        for (auto &p : m->tk) {
+            if (p) (void)hipFree(p);
+            p = nullptr;
         }
         m->tk_cap = 0;
-        for (int i = 0; i < 2; ++i) {
-            L_HIP(m, hipMalloc(&m->tk_key[i], sizeof(float) * need), "hipMalloc(top-k)");
-            L_HIP(m, hipMalloc(&m->tk_idx[i], sizeof(int) * need), "hipMalloc(top-k)");
-        }
+        for (auto &p : m->tk) L_HIP(m, hipMalloc(&p, sizeof(unsigned long long) * need), "hipMalloc(top-k)");
         m->tk_cap = need;
     }
-    L_HIP(m, mlp_topk(keys, n, k, m->tk_key, m->tk_idx, idx, m->stream), "top-k launch");
+    L_HIP(m, mlp_topk(keys, n, k, m->tk, idx, m->stream), "top-k launch");
     L_HIP(m, hipStreamSynchronize(m->stream), "hipStreamSynchronize");
     return PWA_OK;
 }
