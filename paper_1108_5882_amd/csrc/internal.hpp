@@ -282,7 +282,7 @@ struct MlpBuffers {
     _Float16 *fact = nullptr;
     float *fvec = nullptr;
     _Float16 *fwh = nullptr;          // fp16 W1 [256][128], W2 [256][256], W2^T [256][256]
-    int *ftnext = nullptr;            // Adam step of the pending update (device)
+    int *ftnext = nullptr;            // Adam step of the pending update and its two corrections (device, 3 words)
 };
 
 int64_t mlp_param_count(int in, int hidden);

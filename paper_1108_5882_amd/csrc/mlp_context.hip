@@ -167,7 +167,7 @@ pwa_status pwa_mlp_create(pwa_mlp **out, int device, int32_t in, int32_t hidden,
         (st = alloc(m, &b.lrow, max_batch)) || (st = alloc(m, &b.loss, 1)) ||
         (st = alloc(m, &b.Xb, (size_t)max_batch * in)) || (st = alloc(m, &b.tb, max_batch)) ||
         (st = alloc(m, &b.ws, (size_t)mlp_workspace_floats(in, hidden))) ||
-        (st = alloc(m, &ints, 4))) {
+        (st = alloc(m, &ints, 6))) {
         g_lerr = m->err;
         pwa_mlp_destroy(m);
         return st;
@@ -189,7 +189,7 @@ pwa_status pwa_mlp_create(pwa_mlp **out, int device, int32_t in, int32_t hidden,
     if (e == hipSuccess) e = hipMemsetAsync(b.P, 0, sizeof(float) * b.nparams, m->stream);
     if (e == hipSuccess) e = hipMemsetAsync(b.M1, 0, sizeof(float) * b.nparams, m->stream);
     if (e == hipSuccess) e = hipMemsetAsync(b.M2, 0, sizeof(float) * b.nparams, m->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(ints, 0, sizeof(int) * 4, m->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(ints, 0, sizeof(int) * 6, m->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
     if (e != hipSuccess) {
         g_lerr = std::string("initialisation: ") + hipGetErrorString(e);
