@@ -29,6 +29,7 @@
 // which a second kernel adds in block order (FP64) before forming NLL and
 // gradient per vector.
 #include "internal.hpp"
+#include "lane_ops.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -442,78 +443,131 @@ __global__ __launch_bounds__(kThreads) void nll_batch_kernel(BatchArgs p) {
         batch_block<KS, CT, 1, REF>(p, bufs, (int)blockIdx.x - p.nb[0]);
 }
 
-// Exact terms of the flagged data events: block (b, y) and its wave w take the
-// flag words of data block b's tiles for vector group 8 y + w, in tile, word and
-// bit order, and add each flagged event's terms, in the units of the block
-// partials (log2 I, conj(A) z / (I t_v)), to the partial of its
-// vector and block: every partial is updated by one wave, in a fixed order.
-// z is formed in FP64 from the FP32 amplitudes (one wave per event, lanes over
-// waves a), like the single-V path.
-template <int CT>
+// Exact terms of the flagged data events, in the units of the block partials
+// (log2 I, conj(A) z / (I t_v)), added to the partial of their vector and block:
+// block (b, y) takes the flag words of data block b's tiles for the vector groups
+// 8 y .. 8 y + 7.  A wave takes one group, or with fewer groups than waves a share
+// of its vectors.  It reads 512 words at a time and goes through its vectors: the
+// vector's flagged events are listed in tile, word and bit order, SG lanes (lane =
+// wave a) form each event's z in FP64 from the FP32 amplitudes, like the single-V
+// path, 64 / SG events side by side and four such rounds of rows in flight, and
+// the terms are added to the partial in list order.  Every partial is updated by
+// one wave, in that fixed order.
+//
+// Bound: latency (flag words, then rows; few events are flagged).  256 vectors at
+// K = 32, 2 10^6 data rows: 128 us; 32 vectors at K = 8 on 4000 rows (one group):
+// 5.6 us on average over a fit.  201 and 13.3 us when one wave per group took one
+// event after the other, each with a row load, twelve lane shuffles through LDS
+// and an update of the partial in memory.
+constexpr int kRefineLoads = 8;                     // flag words per lane and chunk
+constexpr int kRefineRounds = 4;                    // rounds of rows in flight
+constexpr unsigned long long kEveryRow16 = 0x0001000100010001ull;
+
+template <int CT, int SG>
 __global__ __launch_bounds__(kThreads) void batch_refine_kernel(BatchArgs p) {
     constexpr int kVPerWave = 8 * CT;
     constexpr int kWords = 8 * (CT / 2);
-    constexpr int kLoads = 4;                       // flag words in flight per lane
+    constexpr int E = 64 / SG;                      // events side by side
+    __shared__ unsigned short list[kWaves][64 * kRefineLoads * 4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int vg = (int)blockIdx.y * kWaves + wave;
-    const int v0 = vg * kVPerWave;
-    if (v0 >= p.nv) return;
-    const int64_t n = p.n[0];
-    const int64_t ntiles = (n + kTile - 1) / kTile;
+    const int a = lane & (SG - 1), es = lane / SG;
+    // waves per vector group: a power of two
+    const int ng = min(kWaves, (p.nv + kVPerWave - 1) / kVPerWave - (int)blockIdx.y * kWaves);
+    int sub = 1;
+    while (2 * sub * ng <= kWaves) sub *= 2;
+    if (wave >= ng * sub) return;
+    const int vg = (int)blockIdx.y * kWaves + wave / sub;
+    const int c0 = 16 / sub * (wave % sub), c1 = c0 + 16 / sub;      // vectors 16 g + c0 .. 16 g + c1 - 1
+    const unsigned long long mine = (((1ull << (c1 - c0)) - 1) << c0) * kEveryRow16;
+    const int64_t ntiles = (p.n[0] + kTile - 1) / kTile;
     const int64_t tile0 = (int64_t)blockIdx.x * p.tpb;
     const int64_t tile1 = tile0 + p.tpb < ntiles ? tile0 + p.tpb : ntiles;
-    const int nblk = p.nb[0] + p.nb[1];
-    const int k = p.k;
-    // this wave's words for tiles [tile0, tile1) are contiguous: the lanes read
-    // 64 of them per load and the wave visits only the nonzero ones, in order
+    const int nblk = p.nb[0] + p.nb[1], k = p.k;
+    unsigned short *events = list[wave];
+    const unsigned long long below = (1ull << lane) - 1;
+    // the group's words for tiles [tile0, tile1) are contiguous
     const int64_t nwords = (tile1 - tile0) * kWords;
     const unsigned long long *fw = p.flags + ((int64_t)vg * ntiles + tile0) * kWords;
-    for (int64_t base = 0; base < nwords; base += 64 * kLoads) {
-        unsigned long long mw[kLoads];
+    for (int64_t base = 0; base < nwords; base += 64 * kRefineLoads) {
+        unsigned long long mw[kRefineLoads], any = 0;
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) {
+        for (int j = 0; j < kRefineLoads; ++j) {
             const int64_t i = base + 64 * j + lane;
             mw[j] = i < nwords ? fw[i] : 0ull;
         }
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) {
-            unsigned long long nz = __ballot(mw[j] != 0ull);
-            while (nz) {
-                const int src = __builtin_ctzll(nz);
-                nz &= nz - 1;
-                unsigned long long m = __shfl(mw[j], src);
-                const int64_t i = base + 64 * j + src;
-                const int64_t t = tile0 + i / kWords;
-                const int wi = (int)(i % kWords);
-                const int g = wi / 8, rt = (wi % 8) / 4, e = wi % 4;
-                while (m) {
-                    const int l = __builtin_ctzll(m);
-                    m &= m - 1;
-                    const int ev = 16 * rt + 4 * (l >> 4) + e;
-                    const int v = v0 + 16 * g + (l & 15);
-                    const int64_t row = t * kTile + ev;
-                    const double *V = p.V + (int64_t)v * p.vstride;
-                    double ar = 0.0, ai = 0.0, zr = 0.0, zi = 0.0;
-                    if (lane < k) {
-                        ar = (double)p.A[0][2 * (row * p.ld + lane)];
-                        ai = (double)p.A[0][2 * (row * p.ld + lane) + 1];
-                        zr = V[2 * lane] * ar - V[2 * lane + 1] * ai;
-                        zi = V[2 * lane] * ai + V[2 * lane + 1] * ar;
+        for (int j = 0; j < kRefineLoads; ++j) any |= mw[j] &= mine;
+        if (!__ballot(any != 0)) continue;
+        for (int c = c0; c < c1; ++c) {
+            if (!__ballot((any >> c & kEveryRow16) != 0)) continue;
+            for (int g = 0; g < CT / 2; ++g) {
+                // this vector's bits (word i of a chunk belongs to column group (i % kWords) / 8)
+                const bool my_g = lane % kWords / 8 == g;
+                int total = 0;
+#pragma unroll
+                for (int j = 0; j < kRefineLoads; ++j) {
+                    const unsigned long long bits = my_g ? mw[j] >> c & kEveryRow16 : 0ull;
+                    if (!__ballot(bits != 0)) continue;
+                    int at = total, here = 0;
+                    unsigned long long row[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        row[q] = __ballot((bits >> (16 * q) & 1) != 0);
+                        at += __popcll(row[q] & below);
+                        total += __popcll(row[q]);
                     }
 #pragma unroll
-                    for (int off = 1; off < 64; off <<= 1) {
-                        zr += __shfl_xor(zr, off);
-                        zi += __shfl_xor(zi, off);
+                    for (int q = 0; q < 4; ++q)
+                        if (bits >> (16 * q) & 1) events[at + here++] = (unsigned short)((64 * j + lane) * 4 + q);
+                }
+                if (total == 0) continue;
+                // LDS operations of one wave complete in order; the fences keep the compiler's order
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                const int v = vg * kVPerWave + 16 * g + c;
+                const double *V = p.V + (int64_t)v * p.vstride;
+                const double vr = a < k ? V[2 * a] : 0.0, vi = a < k ? V[2 * a + 1] : 0.0, tv = p.vscale[v];
+                double *dst = p.partials + ((int64_t)v * nblk + blockIdx.x) * p.pstride;
+                double acc_t = dst[0], acc_r = a < k ? dst[1 + 2 * a] : 0.0, acc_i = a < k ? dst[2 + 2 * a] : 0.0;
+                for (int s = 0; s < total; s += E * kRefineRounds) {
+                    float2 x[kRefineRounds];
+#pragma unroll
+                    for (int u = 0; u < kRefineRounds; ++u) {
+                        const int i = s + u * E + es;
+                        x[u] = float2{0.f, 0.f};
+                        if (i < total && a < k) {
+                            const int q = events[i] & 3;
+                            const int64_t w = base + (events[i] >> 2);
+                            const int wi = (int)(w % kWords) % 8;
+                            const int64_t r = (tile0 + w / kWords) * kTile + 16 * (wi / 4) + 4 * q + wi % 4;
+                            x[u] = *reinterpret_cast<const float2 *>(p.A[0] + 2 * (r * p.ld + a));
+                        }
                     }
-                    const double I = zr * zr + zi * zi;
-                    const double tv = p.vscale[v];
-                    double *dst = p.partials + ((int64_t)v * nblk + blockIdx.x) * p.pstride;
-                    if (lane == 0) dst[0] += log2(I);
-                    if (lane < k) {
+#pragma unroll
+                    for (int u = 0; u < kRefineRounds; ++u) {
+                        if (s + u * E >= total) break;
+                        const double ar = (double)x[u].x, ai = (double)x[u].y;
+                        const double zr = lane_sum<SG>(fma(vr, ar, -(vi * ai)));
+                        const double zi = lane_sum<SG>(fma(vr, ai, vi * ar));
+                        const double I = fma(zr, zr, zi * zi);
                         const double ur = zr / (I * tv), ui = zi / (I * tv);
-                        dst[1 + 2 * lane] += ar * ur + ai * ui;        // Re conj(A_a) u
-                        dst[2 + 2 * lane] += ar * ui - ai * ur;        // Im conj(A_a) u
+                        const double tt = log2(I);
+                        const double tr = fma(ar, ur, ai * ui);          // Re conj(A_a) u
+                        const double ti = fma(ar, ui, -(ai * ur));       // Im conj(A_a) u
+#pragma unroll
+                        for (int e = 0; e < E; ++e) {
+                            if (s + u * E + e >= total) break;
+                            acc_t += E == 1 ? tt : __shfl(tt, e * SG);
+                            acc_r += E == 1 ? tr : __shfl(tr, e * SG + a);
+                            acc_i += E == 1 ? ti : __shfl(ti, e * SG + a);
+                        }
                     }
+                }
+                if (lane == 0) dst[0] = acc_t;
+                if (es == 0 && a < k) {
+                    dst[1 + 2 * a] = acc_r;
+                    dst[2 + 2 * a] = acc_i;
                 }
             }
         }
@@ -870,10 +924,15 @@ hipError_t launch_batch_refine(const BatchArgs &args, hipStream_t stream) {
     if (args.nb[0] == 0) return hipSuccess;
     const int gy = (batch_vector_groups(args.nv, args.k) + kWaves - 1) / kWaves;
     const dim3 grid(args.nb[0], gy);
-    if (batch_ct(args.k) == 4)
-        hipLaunchKernelGGL((batch_refine_kernel<4>), grid, dim3(kThreads), 0, stream, args);
+    // the fewest lanes that hold the event's waves
+    if (args.k <= 8)
+        hipLaunchKernelGGL((batch_refine_kernel<4, 8>), grid, dim3(kThreads), 0, stream, args);
+    else if (args.k <= 16)
+        hipLaunchKernelGGL((batch_refine_kernel<4, 16>), grid, dim3(kThreads), 0, stream, args);
+    else if (args.k <= 32)
+        hipLaunchKernelGGL((batch_refine_kernel<4, 32>), grid, dim3(kThreads), 0, stream, args);
     else
-        hipLaunchKernelGGL((batch_refine_kernel<2>), grid, dim3(kThreads), 0, stream, args);
+        hipLaunchKernelGGL((batch_refine_kernel<2, 64>), grid, dim3(kThreads), 0, stream, args);
     return hipGetLastError();
 }
 

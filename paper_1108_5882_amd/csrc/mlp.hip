@@ -13,6 +13,7 @@
 // master weights.  The kernels of a training step are captured in HIP graphs
 // (one step, and groups of 16 steps) and replayed.
 #include "internal.hpp"
+#include "lane_ops.hpp"
 
 #include <cmath>
 
@@ -409,29 +410,6 @@ __device__ __forceinline__ u64 order_of(float key, int index) {
     return ((u64)(b & 0x80000000u ? ~b : b | 0x80000000u) << 32) | (unsigned)index;
 }
 
-// value of lane ^ M
-template <int M>
-__device__ __forceinline__ unsigned lane_xor(unsigned x) {
-    if constexpr (M == 1) return __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, true);     // quad_perm [1,0,3,2]
-    if constexpr (M == 2) return __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, true);     // quad_perm [2,3,0,1]
-    if constexpr (M == 4)                                                                     // lane ^ 3, then ^ 7
-        return __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, x, 0x1B, 0xF, 0xF, true), 0x141, 0xF, 0xF,
-                                           true);
-    if constexpr (M == 8) return __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, true);    // row_ror 8
-    if constexpr (M == 16) {
-        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-        return (threadIdx.x & 16) ? r[0] : r[1];
-    }
-    if constexpr (M == 32) {
-        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-        return (threadIdx.x & 32) ? r[0] : r[1];
-    }
-}
-template <int M>
-__device__ __forceinline__ u64 lane_xor64(u64 x) {
-    return ((u64)lane_xor<M>((unsigned)(x >> 32)) << 32) | lane_xor<M>((unsigned)x);
-}
-
 // A wave's list: 64 E numbers, number i = E lane + r in register r of a lane.
 // One compare-exchange step at distance S within ascending and descending runs
 // of `size` (size 0: the whole list ascends).
@@ -453,7 +431,7 @@ __device__ __forceinline__ void exchange(u64 (&v)[E], int size, int lane) {
 #pragma unroll
         for (int r = 0; r < E; ++r) {
             const bool small = ((E * lane & S) == 0) == ((E * lane & size) == 0);
-            const u64 a = v[r], b = lane_xor64<S / E>(a);
+            const u64 a = v[r], b = lane_xor<S / E>(a);
             v[r] = small == (b < a) ? b : a;
         }
     }
