@@ -30,11 +30,9 @@ def sources():
     return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
 
 
-# Per-source additions.  FP64 MFMA accumulators in VGPRs: hessian.hip's
-# loop-carried tiles otherwise bounce between the VGPR and AGPR files, and
-# gram.hip's take twice the registers (one wave per SIMD from 33 waves on
-# instead of two or three).
-SOURCE_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("hessian.hip", "gram.hip")}
+# Per-source additions.  hessian.hip: FP64 MFMA accumulators in VGPRs (its
+# loop-carried tiles otherwise bounce between the VGPR and AGPR files).
+SOURCE_FLAGS = {"hessian.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _compile(src: str) -> str:

@@ -245,7 +245,6 @@ hipError_t launch_pad_check(pwa_prec prec, const void *A, int64_t n, int64_t ld,
 hipError_t launch_gram(pwa_prec prec, const void *A, const void *w, int64_t n, int64_t ld, int k,
                        double n_gen, double *partials, int blocks, double *M, hipStream_t stream);
 size_t gram_partial_doubles(int k, int blocks);
-int gram_blocks(int cu_count, int k, int64_t n);
 
 // Hessian of the NLL in the real parameters (hessian.hip): one pass over the n
 // data rows (A, row stride ld complex) at V (2k doubles, host; passed to the
