@@ -64,6 +64,8 @@ struct pwa_ctx {
     int extended = 0;
     double *gram = nullptr;          // k x k complex FP64 (1/N_gen folded)
     bool gram_valid = false;
+    void *g_buf = nullptr;           // block partials of the matrix's build
+    size_t g_cap = 0;
 
     double *partials = nullptr;      // block partials, then group sums (stream_scratch_doubles)
     double *gsums = nullptr;
@@ -191,6 +193,17 @@ void split_blocks(const pwa_ctx *ctx, int64_t n0, int64_t n1, int32_t nb[2]) {
     stream_grid(ctx->cfg, (int64_t)ctx->cu_count * ctx->cfg.blocks_per_cu, n0, n1, nb);
 }
 
+// Grows a device scratch buffer to at least `bytes`.
+pwa_status grow(pwa_ctx *ctx, void **buf, size_t *cap, size_t bytes, const char *what) {
+    if (*cap >= bytes) return PWA_OK;
+    if (*buf) (void)hipFree(*buf);
+    *buf = nullptr;
+    *cap = 0;
+    PWA_HIP(ctx, hipMalloc(buf, bytes), what);
+    *cap = bytes;
+    return PWA_OK;
+}
+
 pwa_status ensure_gram(pwa_ctx *ctx) {
     if (ctx->gram_valid) return PWA_OK;
     const Sample &mc = ctx->s[1];
@@ -201,15 +214,13 @@ pwa_status ensure_gram(pwa_ctx *ctx) {
                 "hipMemsetAsync(gram)");
     } else {
         const int blocks = (int)std::min<int64_t>((int64_t)ctx->cu_count * 2, (mc.n + 63) / 64);
-        double *scratch = nullptr;
-        PWA_HIP(ctx, hipMalloc(&scratch, sizeof(double) * gram_partial_doubles(ctx->k, blocks)),
-                "hipMalloc(gram scratch)");
-        hipError_t e = launch_gram(ctx->prec, mc.A, mc.w, mc.n, ctx->ld, ctx->k, mc.n_gen, scratch,
-                                   blocks, ctx->gram, ctx->stream);
-        hipError_t e2 = hipStreamSynchronize(ctx->stream);
-        (void)hipFree(scratch);
-        if (e != hipSuccess) return hip_fail(ctx, e, "gram kernel");
-        if (e2 != hipSuccess) return hip_fail(ctx, e2, "gram kernel");
+        // everything that reads the matrix is ordered after its build on the context's stream
+        pwa_status st = grow(ctx, &ctx->g_buf, &ctx->g_cap, sizeof(double) * gram_partial_doubles(ctx->k, blocks),
+                             "hipMalloc(gram partials)");
+        if (st != PWA_OK) return st;
+        PWA_HIP(ctx, launch_gram(ctx->prec, mc.A, mc.w, mc.n, ctx->ld, ctx->k, mc.n_gen,
+                                 static_cast<double *>(ctx->g_buf), blocks, ctx->gram, ctx->stream),
+                "gram kernel");
     }
     ctx->gram_valid = true;
     return PWA_OK;
@@ -341,17 +352,6 @@ pwa_status eval_sync(pwa_ctx *ctx, const double *V, double *nll, double *grad) {
     if (grad)
         for (int i = 0; i < 2 * k; ++i) grad[i] = res[1 + i];
     if (ctx->last_flags) return fail(ctx, PWA_E_DOMAIN, "non-positive intensity or normalisation");
-    return PWA_OK;
-}
-
-// Grows a device scratch buffer to at least `bytes`.
-pwa_status grow(pwa_ctx *ctx, void **buf, size_t *cap, size_t bytes, const char *what) {
-    if (*cap >= bytes) return PWA_OK;
-    if (*buf) (void)hipFree(*buf);
-    *buf = nullptr;
-    *cap = 0;
-    PWA_HIP(ctx, hipMalloc(buf, bytes), what);
-    *cap = bytes;
     return PWA_OK;
 }
 
@@ -813,7 +813,7 @@ pwa_status pwa_destroy(pwa_ctx *ctx) {
     if (ctx->counters) (void)hipFree(ctx->counters);
     if (ctx->gram) (void)hipFree(ctx->gram);
     for (void *b : {ctx->b_wfrag, ctx->b_ascale, ctx->b_vscale, ctx->b_V, ctx->b_partials, ctx->b_out,
-                    (void *)ctx->b_amax, (void *)ctx->b_rnorm, ctx->b_flags, ctx->h_buf, ctx->b_planes[0],
+                    (void *)ctx->b_amax, (void *)ctx->b_rnorm, ctx->b_flags, ctx->h_buf, ctx->g_buf, ctx->b_planes[0],
                     ctx->b_planes[1]})
         if (b) (void)hipFree(b);
     if (ctx->partials) (void)hipFree(ctx->partials);
