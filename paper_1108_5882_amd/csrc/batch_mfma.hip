@@ -30,6 +30,7 @@
 // gradient per vector.
 #include "internal.hpp"
 #include "lane_ops.hpp"
+#include "lbfgs_device.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -118,12 +119,10 @@ __device__ __forceinline__ void batch_block(const BatchArgs &p, BatchSmem<KS, CT
         thr[g] = -1.f;
         inv_t2[g] = 1.f;
         const int v = v0 + 16 * g + r16;
-        if (SEG == 0 && v < p.nv) inv_t2[g] = (float)(1.0 / (p.vscale[v] * p.vscale[v]));
-        if (kRef && v < p.nv) {
-            const double *Vv = p.V + (int64_t)v * p.vstride;
-            double n2 = 0.0;
-            for (int a = 0; a < 2 * p.k; ++a) n2 += Vv[a] * Vv[a];
-            thr[g] = (float)((double)p.cthr2 * p.vscale[v] * p.vscale[v] * n2);
+        if (SEG == 0 && v < p.nv) {
+            const double tv = p.vscale[2 * v], n2 = p.vscale[2 * v + 1];
+            inv_t2[g] = (float)(1.0 / (tv * tv));
+            if (kRef) thr[g] = (float)((double)p.cthr2 * tv * tv * n2);
         }
     }
 
@@ -527,7 +526,7 @@ __global__ __launch_bounds__(kThreads) void batch_refine_kernel(BatchArgs p) {
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                 const int v = vg * kVPerWave + 16 * g + c;
                 const double *V = p.V + (int64_t)v * p.vstride;
-                const double vr = a < k ? V[2 * a] : 0.0, vi = a < k ? V[2 * a + 1] : 0.0, tv = p.vscale[v];
+                const double vr = a < k ? V[2 * a] : 0.0, vi = a < k ? V[2 * a + 1] : 0.0, tv = p.vscale[2 * v];
                 double *dst = p.partials + ((int64_t)v * nblk + blockIdx.x) * p.pstride;
                 double acc_t = dst[0], acc_r = a < k ? dst[1 + 2 * a] : 0.0, acc_i = a < k ? dst[2 + 2 * a] : 0.0;
                 for (int s = 0; s < total; s += E * kRefineRounds) {
@@ -652,6 +651,69 @@ __device__ __forceinline__ WeightSplit split_weight(double x) {
     return WeightSplit{hi, (_Float16)(float)(x - (double)(float)hi)};
 }
 
+// Forward weights of one vector by one wave: lane i holds elements i and i + 64 of
+// V (those past 2k are not used) and the scales of their columns.  t_v is the power of two with
+// max_a |V_a| / s_a * t_v in [2^13, 2^14); W' = W t_v / s_r is split into FP16 hi +
+// lo and stored in the B-operand fragment order [group][hi/lo][ct][ks][lane][8] that
+// the batched kernel loads; a vector past nv stores zeros.  (t_v, |V|^2) go to
+// vscale; |V|^2 is added in index order from the lanes' values in LDS (vs, 128 doubles).
+// p.vscale and p.wfrag are outputs here.
+template <int KS, int CT>
+__device__ __forceinline__ void vector_weights(const BatchArgs &p, int v, const LbVec &V, const float (&sc)[kLbfgsPer],
+                                               double *vs) {
+    const int lane = threadIdx.x & 63;
+    double m = 0.0;
+#pragma unroll
+    for (int u = 0; u < kLbfgsPer; ++u) {
+        const double s = (double)__shfl(sc[u], lane & ~1);
+        if (lane + 64 * u < 2 * p.k) m = fmax(m, fabs(V.e[u]) / s);
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) m = fmax(m, __shfl_xor(m, off));
+    double t = 1.0;
+    if (m > 0.0) {
+        int e;
+        frexp(m, &e);                 // m in [2^(e-1), 2^e)
+        t = ldexp(1.0, 14 - e);
+    }
+    const int grp = v / (8 * CT), ct = v % (8 * CT) / 16 * 2, col = v % 16;
+    const LbVec o = lb_pair(V);
+    _Float16 *wf = reinterpret_cast<_Float16 *>(const_cast<void *>(p.wfrag));
+#pragma unroll
+    for (int u = 0; u < kLbfgsPer; ++u) {
+        const int r = lane + 64 * u;
+        if (r >= 32 * KS) continue;
+        const size_t at = ((size_t)(r / 32) * 64 + 16 * (r % 32 / 8) + col) * 8 + r % 8;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {                 // the columns of z's real and imaginary part
+            const double w = c == 0 ? (lane & 1 ? -V.e[u] : V.e[u]) : o.e[u];
+            const WeightSplit ws = split_weight(r < 2 * p.k ? w * t / (double)sc[u] : 0.0);
+            wf[(((size_t)grp * 2 + 0) * CT + ct + c) * KS * 512 + at] = ws.hi;
+            wf[(((size_t)grp * 2 + 1) * CT + ct + c) * KS * 512 + at] = ws.lo;
+        }
+    }
+    if (v >= p.nv) return;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+#pragma unroll
+    for (int u = 0; u < kLbfgsPer; ++u) vs[lane + 64 * u] = V.e[u];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    double n2 = 0.0;
+#pragma unroll 8
+    for (int i = 0; i < 2 * p.k; ++i) n2 = fma(vs[i], vs[i], n2);
+    if (lane == 0) {
+        double *vsc = const_cast<double *>(p.vscale);
+        vsc[2 * v] = t;
+        vsc[2 * v + 1] = n2;
+    }
+}
+
+// The scales of the columns that lane i's elements i and i + 64 belong to.
+__device__ __forceinline__ void lane_scales(const BatchArgs &p, float (&sc)[kLbfgsPer]) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int u = 0; u < kLbfgsPer; ++u) sc[u] = lane + 64 * u < 2 * p.k ? p.ascale[lane + 64 * u] : 1.f;
+}
+
 // Per vector v (one block each): add the block partials of each segment in
 // block order, undo the per-vector scale t_v of the forward weights, and form
 // NLL and gradient (Eq. 2 or Eq. 3 form; streamed MC or the MC matrix).
@@ -664,110 +726,197 @@ __device__ __forceinline__ WeightSplit split_weight(double x) {
 //   sum_j w_j I_j(V) = sum_j w_j I_j(V~) + 2 Re sum_a dV_a conj(H_a),
 // with G_a = sum_i conj(A_ia) z_i / I_i and H_a = sum_j w_j conj(A_ja) z_j
 // (the second-order terms are about 2^-44 of the sums).
-// The block partials of a segment are summed by G = kCombineThreads / pstride
-// thread groups (group g takes blocks g, g + G, ...; threads of a group take
-// the pstride values of a block, so each block's partial row is read
-// contiguously; eight loads in flight per thread), then the G group sums are
-// added in group order: the order is fixed.  One block per vector reads a few
-// MB of partials, so the block is large to keep many loads in flight.
-constexpr int kCombineThreads = 1024;
+// The block partials of a segment are summed by G = kCombineSlots / pstride
+// groups (group g takes blocks g, g + G, ...; slots of a group take the pstride
+// values of a block, so each block's partial row is read contiguously), then the
+// G group sums are added in group order: the order is fixed.  A thread holds four
+// slots of both segments, four loads of each in flight: one block per vector
+// reads up to a few MB of partials.  t_v is a power of two, so its reciprocal and the
+// products with either are exact.
+//
+// All threads of the block call it; the results are valid in wave 0 (the NLL, the
+// domain flag and the gradient's elements of the lane).
+constexpr int kCombineThreads = 256;
+constexpr int kCombineSlots = 1024;
 
-__global__ __launch_bounds__(kCombineThreads) void nll_batch_combine_kernel(BatchArgs p) {
-    __shared__ double tot[2][1 + 2 * PWA_MAX_K];
-    __shared__ double grp[kCombineThreads];
-    __shared__ double mv[2 * PWA_MAX_K];
-    __shared__ double dv[2 * PWA_MAX_K];
-    __shared__ double s_c;
-    const int v = blockIdx.x, tid = threadIdx.x;
+struct CombineSmem {
+    double tot[2][1 + 2 * PWA_MAX_K];
+    double grp[2][kCombineSlots];
+    double V[2 * PWA_MAX_K], dv[2 * PWA_MAX_K], mv[2 * PWA_MAX_K];
+    double pl[64 * kLbfgsPer], ps[64 * kLbfgsPer];
+};
+
+__device__ __forceinline__ void combine_vector(const BatchArgs &p, int v, CombineSmem &sm, double &nll, unsigned &flags,
+                                               LbVec &grad) {
+    constexpr int kSlots = kCombineSlots / kCombineThreads;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int pst = p.pstride;
     const int nblk = p.nb[0] + p.nb[1];
     const int k = p.k;
     const double *base = p.partials + (int64_t)v * nblk * pst;
-    const int G = kCombineThreads / pst, g = tid / pst, cc = tid % pst;
-    for (int sg = 0; sg < 2; ++sg) {
-        const int b0 = sg ? p.nb[0] : 0, b1 = sg ? nblk : p.nb[0];
-        if (g < G) {
-            double s = 0.0;
-#pragma unroll 8
-            for (int b = b0 + g; b < b1; b += G) s += base[(int64_t)b * pst + cc];
-            grp[tid] = s;
-        }
-        __syncthreads();
-        if (tid < pst) {
-            double s = 0.0;
-            for (int h = 0; h < G; ++h) s += grp[h * pst + tid];
-            tot[sg][tid] = s;
-        }
-        __syncthreads();
-    }
-    const double tv = p.vscale[v];
-    const double *V = p.V + (int64_t)v * p.vstride;
+    const int G = kCombineSlots / pst;
+    const double tv = p.vscale[2 * v], itv = 1.0 / tv;
     for (int i = tid; i < 2 * k; i += kCombineThreads) {
-        const double sr = (double)p.ascale[i];
-        const WeightSplit ws = split_weight(V[i] * tv / sr);
-        dv[i] = V[i] - ((double)ws.hi + (double)ws.lo) * sr / tv;
+        const double x = p.V[(int64_t)v * p.vstride + i], sr = (double)p.ascale[i];
+        const WeightSplit ws = split_weight(x * tv / sr);
+        sm.V[i] = x;
+        sm.dv[i] = x - ((double)ws.hi + (double)ws.lo) * sr * itv;
+    }
+    constexpr int kAhead = 4;
+    double s[2][kSlots];
+    int off[kSlots], b[kSlots];
+#pragma unroll
+    for (int u = 0; u < kSlots; ++u) {
+        const int slot = tid + u * kCombineThreads;
+        s[0][u] = s[1][u] = 0.0;
+        off[u] = slot % pst;
+        b[u] = slot < G * pst ? slot / pst : nblk;              // blocks b, b + G, ... of both segments
+    }
+    // every slot's terms in block order; a slot past its last block reads that block and keeps its sum
+    for (int j = 0; j < max(p.nb[0], p.nb[1]); j += kAhead * G) {
+        double x[2][kAhead][kSlots];
+#pragma unroll
+        for (int sg = 0; sg < 2; ++sg) {
+            const double *seg = base + (sg ? (int64_t)p.nb[0] * pst : 0);
+            if (j < p.nb[sg]) {
+#pragma unroll
+                for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+                    for (int u = 0; u < kSlots; ++u)
+                        x[sg][i][u] = seg[(int64_t)min(b[u] + j + i * G, p.nb[sg] - 1) * pst + off[u]];
+            }
+        }
+#pragma unroll
+        for (int sg = 0; sg < 2; ++sg)
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+                for (int u = 0; u < kSlots; ++u)
+                    if (b[u] + j + i * G < p.nb[sg]) s[sg][u] += x[sg][i][u];
+    }
+#pragma unroll
+    for (int sg = 0; sg < 2; ++sg)
+#pragma unroll
+        for (int u = 0; u < kSlots; ++u) sm.grp[sg][tid + u * kCombineThreads] = s[sg][u];
+    __syncthreads();
+    for (int i = tid; i < 2 * pst; i += kCombineThreads) {
+        const int sg = i >= pst, c = i - sg * pst;
+        double s = 0.0;
+#pragma unroll 8
+        for (int h = 0; h < G; ++h) s += sm.grp[sg][h * pst + c];
+        sm.tot[sg][c] = s;
     }
     if (p.gram) {
         for (int a = tid; a < k; a += kCombineThreads) {
             double r = 0.0, i = 0.0;
             for (int b = 0; b < k; ++b) {
                 const double mr = p.gram[2 * (a * k + b)], mi = p.gram[2 * (a * k + b) + 1];
-                r += mr * V[2 * b] - mi * V[2 * b + 1];
-                i += mr * V[2 * b + 1] + mi * V[2 * b];
+                r += mr * sm.V[2 * b] - mi * sm.V[2 * b + 1];
+                i += mr * sm.V[2 * b + 1] + mi * sm.V[2 * b];
             }
-            mv[2 * a] = r;
-            mv[2 * a + 1] = i;
+            sm.mv[2 * a] = r;
+            sm.mv[2 * a + 1] = i;
         }
     }
     __syncthreads();
-    double *out = p.out + (int64_t)v * p.ostride;
-    if (tid == 0) {
-        const double nd = p.nd_total;
-        // Z' = t_v z: the data sums hold log2 I (unscaled) and conj(A) u / t_v; sum w I = sum w I' / t_v^2
-        // first-order terms of the weight rounding (data: G = t_v x data sums;
-        // MC: H = MC sums / t_v); the data's log sum is of the unscaled I
-        double dlog = 0.0, ds = 0.0;
-        for (int i = 0; i < 2 * k; ++i) {
-            dlog += dv[i] * tot[0][1 + i] * tv;
-            ds += dv[i] * tot[1][1 + i] / tv;
+    if (tid >= 64) return;
+    // Z' = t_v z: the data sums hold log2 I (unscaled) and conj(A) u / t_v; sum w I = sum w I' / t_v^2
+    // first-order terms of the weight rounding (data: G = t_v x data sums;
+    // MC: H = MC sums / t_v); the data's log sum is of the unscaled I
+    const double nd = p.nd_total;
+#pragma unroll
+    for (int u = 0; u < kLbfgsPer; ++u) {
+        const int i = lane + 64 * u;
+        if (i < 2 * k) {
+            sm.pl[i] = sm.dv[i] * sm.tot[0][1 + i] * tv;
+            sm.ps[i] = sm.dv[i] * sm.tot[1][1 + i] * itv;
         }
-        const double sum_log = tot[0][0] * 0.69314718055994530942 + 2.0 * dlog;
-        double S, c;
-        if (p.gram) {
-            double s = 0.0;
-            for (int a = 0; a < k; ++a) s += V[2 * a] * mv[2 * a] + V[2 * a + 1] * mv[2 * a + 1];
-            S = s;
-            c = p.extended ? 1.0 : nd / S;
-        } else {
-            const double s_raw = tot[1][0] / (tv * tv) + 2.0 * ds;
-            S = s_raw / p.n_gen;
-            c = p.extended ? 1.0 / p.n_gen : nd / s_raw;
-        }
-        double nll;
-        unsigned flags = 0;
-        if (!p.extended && nd == 0.0) {
-            nll = 0.0;
-            c = 0.0;
-        } else {
-            nll = p.extended ? -sum_log + S : -sum_log + nd * log(S);
-            if (!isfinite(nll) || (!p.extended && !(S > 0.0))) {
-                nll = INFINITY;
-                flags = 1;
-            }
-        }
-        out[0] = nll;
-        out[1 + 2 * k] = (double)flags;
-        s_c = c;
     }
-    __syncthreads();
-    const double c = s_c;
-    const bool zero = !p.extended && p.nd_total == 0.0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    double dlog = 0.0, ds = 0.0;
+#pragma unroll 8
+    for (int i = 0; i < 2 * k; ++i) {
+        dlog += sm.pl[i];
+        ds += sm.ps[i];
+    }
+    const double sum_log = sm.tot[0][0] * 0.69314718055994530942 + 2.0 * dlog;
+    double S, c;
+    if (p.gram) {
+        double s = 0.0;
+        for (int a = 0; a < k; ++a) s += sm.V[2 * a] * sm.mv[2 * a] + sm.V[2 * a + 1] * sm.mv[2 * a + 1];
+        S = s;
+        c = p.extended ? 1.0 : nd / S;
+    } else {
+        const double s_raw = sm.tot[1][0] / (tv * tv) + 2.0 * ds;
+        S = s_raw / p.n_gen;
+        c = p.extended ? 1.0 / p.n_gen : nd / s_raw;
+    }
+    const bool zero = !p.extended && nd == 0.0;
+    flags = 0;
+    if (zero) {
+        nll = 0.0;
+        c = 0.0;
+    } else {
+        nll = p.extended ? -sum_log + S : -sum_log + nd * log(S);
+        if (!isfinite(nll) || (!p.extended && !(S > 0.0))) {
+            nll = INFINITY;
+            flags = 1;
+        }
+    }
     // data sums carry u = t_v Z'/I' (x t_v); MC sums carry w Z' = t_v w z (/ t_v)
-    for (int i = tid; i < 2 * k; i += kCombineThreads) {
-        const double g = tot[0][1 + i] * tv;
-        const double h = p.gram ? mv[i] : tot[1][1 + i] / tv;
-        out[1 + i] = zero ? 0.0 : 2.0 * (-g + c * h);
+#pragma unroll
+    for (int u = 0; u < kLbfgsPer; ++u) {
+        const int i = lane + 64 * u;
+        grad.e[u] = 0.0;
+        if (i < 2 * k && !zero) {
+            const double g = sm.tot[0][1 + i] * tv;
+            const double h = p.gram ? sm.mv[i] : sm.tot[1][1 + i] * itv;
+            grad.e[u] = 2.0 * (-g + c * h);
+        }
     }
+}
+
+__global__ __launch_bounds__(kCombineThreads) void nll_batch_combine_kernel(BatchArgs p) {
+    __shared__ CombineSmem sm;
+    const int v = blockIdx.x;
+    double nll;
+    unsigned flags;
+    LbVec grad;
+    combine_vector(p, v, sm, nll, flags, grad);
+    if (threadIdx.x >= 64) return;
+    double *out = p.out + (int64_t)v * p.ostride;
+    lb_store(out + 1, grad, 2 * p.k, threadIdx.x);
+    if (threadIdx.x == 0) {
+        out[0] = nll;
+        out[1 + 2 * p.k] = (double)flags;
+    }
+}
+
+// What lies between two passes of a fit, in one launch: the vector's sums, its
+// L-BFGS update and the weights of its next trial point, which the update leaves in
+// the state (p.V points into it).  Bound by latency; the state is loaded before the
+// partials' sums.  32 vectors at K = 8, 24000 rows: 13.8 us; 23 us in four launches
+// (combine 7.3, update 6.2, scales 4.5, fragments 4.7), one vector's |V|^2
+// formed by every block of the pass (12.6 us, now 8.7).
+template <int KS, int CT>
+__global__ __launch_bounds__(kCombineThreads) void batch_step_kernel(BatchArgs p, LbfgsState *states, double c1,
+                                                                     double ftol, int polar, double rmin) {
+    __shared__ CombineSmem sm;
+    const int v = blockIdx.x, n = 2 * p.k;
+    const bool first = threadIdx.x < 64;
+    LbRegs r;
+    float sc[kLbfgsPer];
+    if (first) {
+        lbfgs_load(r, states + v, n, polar != 0);
+        lane_scales(p, sc);
+    }
+    double nll;
+    unsigned flags;
+    LbVec grad;
+    combine_vector(p, v, sm, nll, flags, grad);
+    if (!first) return;
+    const LbVec next = lbfgs_advance(states + v, r, n, nll, grad, c1, ftol, polar != 0, rmin, sm.pl);
+    vector_weights<KS, CT>(p, v, next, sc, sm.ps);
 }
 
 // Largest |re| or |im| of each wave over a sample's rows (FP32), as float bits
@@ -789,69 +938,30 @@ __global__ void amax_kernel(const float *A, int64_t n, int64_t ld, int k, unsign
     for (int a = threadIdx.x; a < k; a += blockDim.x) atomicMax(&out[a], sm[a]);
 }
 
-// Per vector: power of two t_v with max_a |V_a| / s_a * t_v in [2^13, 2^14).
-__global__ void batch_vscale_kernel(BatchArgs p) {
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= p.nv) return;
-    const double *V = p.V + (int64_t)v * p.vstride;
-    double m = 0.0;
-    for (int a = 0; a < p.k; ++a)
-        m = fmax(m, fmax(fabs(V[2 * a]), fabs(V[2 * a + 1])) / (double)p.ascale[2 * a]);
-    double t = 1.0;
-    if (m > 0.0) {
-        int e;
-        frexp(m, &e);                 // m in [2^(e-1), 2^e)
-        t = ldexp(1.0, 14 - e);
-    }
-    const_cast<double *>(p.vscale)[v] = t;
-}
-
-// Forward weights W' = W t_v / s_r split into FP16 hi + lo, in the B-operand
-// fragment order [group][hi/lo][ct][ks][lane][8] the batched kernel loads.
+// The weights of all vectors, one wave each, the padding groups included.
 template <int KS, int CT>
-__global__ void batch_wfrag_kernel(BatchArgs p, int ngroups_pad) {
-    const int64_t total = (int64_t)ngroups_pad * CT * KS * 64 * 8;
-    _Float16 *wf = reinterpret_cast<_Float16 *>(const_cast<void *>(p.wfrag));
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int e = idx % 8;
-        const int lane = (idx / 8) % 64;
-        const int kk = (idx / (8 * 64)) % KS;
-        const int ct = (idx / (8 * 64 * KS)) % CT;
-        const int grp = (int)(idx / (8 * 64 * KS * CT));
-        const int r = 32 * kk + 8 * (lane >> 4) + e;
-        const int v = grp * 8 * CT + 16 * (ct >> 1) + (lane & 15);
-        double x = 0.0;
-        if (v < p.nv && r < 2 * p.k) {
-            const double *V = p.V + (int64_t)v * p.vstride;
-            const int a = r >> 1;
-            const double vr = V[2 * a], vi = V[2 * a + 1];
-            const double wv = (ct & 1) == 0 ? ((r & 1) == 0 ? vr : -vi) : ((r & 1) == 0 ? vi : vr);
-            x = wv * p.vscale[v] / (double)p.ascale[r];
-        }
-        const WeightSplit ws = split_weight(x);
-        const _Float16 hi = ws.hi, lo = ws.lo;
-        const size_t base = ((((size_t)grp * 2 + 0) * CT + ct) * KS + kk) * 64 + lane;
-        const size_t basel = ((((size_t)grp * 2 + 1) * CT + ct) * KS + kk) * 64 + lane;
-        wf[base * 8 + e] = hi;
-        wf[basel * 8 + e] = lo;
-    }
+__global__ __launch_bounds__(256) void batch_weights_kernel(BatchArgs p, int nvectors) {
+    __shared__ double vs[4][64 * kLbfgsPer];
+    const int wave = threadIdx.x >> 6, v = blockIdx.x * 4 + wave;
+    if (v >= nvectors) return;
+    LbVec V{};
+    float sc[kLbfgsPer];
+    if (v < p.nv) V = lb_load(p.V + (int64_t)v * p.vstride, 2 * p.k, threadIdx.x & 63);
+    lane_scales(p, sc);
+    vector_weights<KS, CT>(p, v, V, sc, vs[wave]);
 }
 
 }  // namespace
 
 hipError_t launch_batch_weights(const BatchArgs &args, hipStream_t stream) {
-    hipLaunchKernelGGL(batch_vscale_kernel, dim3((args.nv + 255) / 256), dim3(256), 0, stream, args);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     const int gpad = (batch_vector_groups(args.nv, args.k) + kWaves - 1) / kWaves * kWaves;
-    const int64_t total = (int64_t)gpad * batch_ct(args.k) * batch_ks(args.k) * 64 * 8;
-    const int blocks = (int)std::min<int64_t>((total + 255) / 256, 4096);
+    const int nvectors = gpad * batch_vectors_per_wave(args.k);
+    const dim3 grid((nvectors + 3) / 4);
     switch (batch_ks(args.k)) {
-        case 1: hipLaunchKernelGGL((batch_wfrag_kernel<1, 4>), dim3(blocks), dim3(256), 0, stream, args, gpad); break;
-        case 2: hipLaunchKernelGGL((batch_wfrag_kernel<2, 4>), dim3(blocks), dim3(256), 0, stream, args, gpad); break;
-        case 3: hipLaunchKernelGGL((batch_wfrag_kernel<3, 2>), dim3(blocks), dim3(256), 0, stream, args, gpad); break;
-        case 4: hipLaunchKernelGGL((batch_wfrag_kernel<4, 2>), dim3(blocks), dim3(256), 0, stream, args, gpad); break;
+        case 1: hipLaunchKernelGGL((batch_weights_kernel<1, 4>), grid, dim3(256), 0, stream, args, nvectors); break;
+        case 2: hipLaunchKernelGGL((batch_weights_kernel<2, 4>), grid, dim3(256), 0, stream, args, nvectors); break;
+        case 3: hipLaunchKernelGGL((batch_weights_kernel<3, 2>), grid, dim3(256), 0, stream, args, nvectors); break;
+        case 4: hipLaunchKernelGGL((batch_weights_kernel<4, 2>), grid, dim3(256), 0, stream, args, nvectors); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -968,6 +1078,22 @@ hipError_t launch_rownorm(const float *A, int64_t n, int64_t ld, int k, float *o
 
 hipError_t launch_batch_combine(const BatchArgs &args, hipStream_t stream) {
     hipLaunchKernelGGL(nll_batch_combine_kernel, dim3(args.nv), dim3(kCombineThreads), 0, stream, args);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_step(const BatchArgs &args, LbfgsState *states, double c1, double ftol, bool polar, double rmin,
+                             hipStream_t stream) {
+    const dim3 grid(args.nv), block(kCombineThreads);
+#define PWA_BATCH_STEP(KS_, CT_)                                                                                     \
+    hipLaunchKernelGGL((batch_step_kernel<KS_, CT_>), grid, block, 0, stream, args, states, c1, ftol, polar ? 1 : 0, \
+                       rmin)
+    switch (batch_ks(args.k)) {
+        case 1: PWA_BATCH_STEP(1, 4); break;
+        case 2: PWA_BATCH_STEP(2, 4); break;
+        case 3: PWA_BATCH_STEP(3, 2); break;
+        default: return hipErrorInvalidValue;          // fits have at most kMultiMaxLd waves
+    }
+#undef PWA_BATCH_STEP
     return hipGetLastError();
 }
 

@@ -446,7 +446,7 @@ pwa_status batch_setup(pwa_ctx *ctx, int32_t nv, BatchArgs &a, int *gpad, bool a
     if ((st = reserve(ctx, alloc, &ctx->b_wfrag, &ctx->b_cap[0],
                       sizeof(_Float16) * (size_t)*gpad * 2 * batch_ct(k) * batch_ks(k) * 64 * 8, "weights")) ||
         (st = reserve(ctx, alloc, &ctx->b_ascale, &ctx->b_cap[1], sizeof(float) * k2, "scales")) ||
-        (st = reserve(ctx, alloc, &ctx->b_vscale, &ctx->b_cap[2], sizeof(double) * nv, "vector scales")) ||
+        (st = reserve(ctx, alloc, &ctx->b_vscale, &ctx->b_cap[2], sizeof(double) * 2 * nv, "vector scales")) ||
         (st = reserve(ctx, alloc, &ctx->b_partials, &ctx->b_cap[4],
                       sizeof(double) * std::max<size_t>(1, batch_partial_doubles(a.n[0], a.n[1], a.tpb, nv, k)),
                       "partials")))
@@ -680,29 +680,21 @@ pwa_status pwa_batch_fit(pwa_ctx *ctx, int32_t nv, const double *V0, int32_t ite
         }
     }
     LbfgsState *d_states = nullptr;
-    double *d_out = nullptr;
-    const int64_t ostride = 2 * k + 2;
     PWA_HIP(ctx, hipMalloc(&d_states, sizeof(LbfgsState) * nv), "hipMalloc(states)");
-    hipError_t e = hipMalloc(&d_out, sizeof(double) * ostride * nv);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(d_states, hs.data(), sizeof(LbfgsState) * nv, hipMemcpyHostToDevice, ctx->stream);
+    hipError_t e = hipMemcpyAsync(d_states, hs.data(), sizeof(LbfgsState) * nv, hipMemcpyHostToDevice, ctx->stream);
     a.V = polar ? d_states[0].vt : d_states[0].xt;
     a.vstride = sizeof(LbfgsState) / sizeof(double);
-    a.out = d_out;
-    a.ostride = ostride;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     if (e == hipSuccess) e = hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
         // the split-3 pass: matrix-core sums with small coherent sums flagged, their
-        // exact recomputation, the combine, then one L-BFGS update per vector
+        // exact recomputation, then the combine, one L-BFGS update per vector and the
+        // next weights
         const bool refine = a.n[0] > 0;
-        hipError_t ec = launch_batch_weights(a, ctx->stream);
-        if (ec == hipSuccess) ec = launch_batch(a, refine, ctx->stream);
+        hipError_t ec = launch_batch(a, refine, ctx->stream);
         if (ec == hipSuccess && refine) ec = launch_batch_refine(a, ctx->stream);
-        if (ec == hipSuccess) ec = launch_batch_combine(a, ctx->stream);
-        if (ec == hipSuccess)
-            ec = launch_lbfgs(nullptr, k, d_out, ostride, d_states, nv, 8, 1e-4, 1e-12, ctx->stream, polar ? 1 : 0, rmin);
+        if (ec == hipSuccess) ec = launch_batch_step(a, d_states, 1e-4, 1e-12, polar, rmin, ctx->stream);
         e = hipStreamEndCapture(ctx->stream, &graph);
         if (ec != hipSuccess) e = ec;
     }
@@ -710,6 +702,7 @@ pwa_status pwa_batch_fit(pwa_ctx *ctx, int32_t nv, const double *V0, int32_t ite
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (e == hipSuccess && avg_ms) e = hipEventCreate(&e0);
     if (e == hipSuccess && avg_ms) e = hipEventCreate(&e1);
+    if (e == hipSuccess && iters > 0) e = launch_batch_weights(a, ctx->stream);
     if (e == hipSuccess && avg_ms) e = hipEventRecord(e0, ctx->stream);
     for (int it = 0; it < iters && e == hipSuccess; ++it) e = hipGraphLaunch(exec, ctx->stream);
     if (e == hipSuccess && avg_ms) e = hipEventRecord(e1, ctx->stream);
@@ -726,7 +719,6 @@ pwa_status pwa_batch_fit(pwa_ctx *ctx, int32_t nv, const double *V0, int32_t ite
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
     (void)hipFree(d_states);
-    if (d_out) (void)hipFree(d_out);
     if (e != hipSuccess) return hip_fail(ctx, e, "batched fit");
     for (int v = 0; v < nv; ++v) {
         const bool started = hs[v].phase != 0;

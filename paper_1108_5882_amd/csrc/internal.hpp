@@ -112,7 +112,7 @@ struct BatchArgs {
     const void *planes[2];     // split operand planes per segment (batch_plane_bytes each)
     const void *wfrag;         // FP16 forward weights in MFMA fragment order
     const float *ascale;       // power-of-two scale per real column (32 * ks entries)
-    const double *vscale;      // power-of-two scale of each vector's weights
+    const double *vscale;      // per vector: power-of-two scale t_v of its weights, |V|^2
     const double *V;           // production vectors (FP64), vector v at V + v * vstride
     int64_t vstride;           // doubles between vectors (>= 2k)
     int64_t ostride;           // doubles between vectors' results in out (>= 2k + 2)
@@ -157,8 +157,8 @@ hipError_t launch_batch_planes(const float *A, int64_t n, int64_t ld, int k, con
                                hipStream_t stream);
 constexpr float kRefineC2 = 1.0f / 64.0f;     // largest c^2 (c = 1/8); batch_setup lowers it as sqrt(k) / N_D
 hipError_t launch_batch_combine(const BatchArgs &args, hipStream_t stream);
-// Device-side forward weights from args.V: the per-vector scales, then the
-// FP16 fragments (args.wfrag, sized for the padded vector groups).
+// Device-side forward weights from args.V: the per-vector scales and |V|^2 (args.vscale),
+// the FP16 fragments (args.wfrag, sized for the padded vector groups).
 hipError_t launch_batch_weights(const BatchArgs &args, hipStream_t stream);
 
 // ---------------------------------------------------------------- multi-fit
@@ -210,15 +210,17 @@ int64_t multi_layout_ld(int k);              // -1 if k is too large
 bool multi_ld_supported(int64_t ld);
 int multi_rows_per_tile(int64_t ld);         // rows one wave covers per tile
 hipError_t launch_multi_eval(const MultiArgs &args, int blocks, hipStream_t stream);
-// One L-BFGS update per fit: fit f has 2 * k_f parameters (k_f = fits[f].k, or
-// k_all when fits is null) and its result [nll, grad] at out + f * ostride.
-// polar: parameters (|V_a|, arg V_a) with |V_a| >= rmin (projected steps),
-// arg V_0 fixed at 0 and phases wrapped into [-pi, pi] after each accepted
-// step; the evaluation reads vt.  Otherwise (Re V_a, Im V_a) and the
-// evaluation reads xt.
-hipError_t launch_lbfgs(const MultiFit *fits, int k_all, const double *out, int64_t ostride,
-                        LbfgsState *states, int nfits, int m, double c1, double ftol,
-                        hipStream_t stream, int polar = 0, double rmin = 0.0);
+// One L-BFGS update per fit in (Re V_a, Im V_a): fit f has 2 fits[f].k parameters
+// and its result [nll, grad] at out + f * ostride; the next evaluation reads xt.
+hipError_t launch_lbfgs(const MultiFit *fits, const double *out, int64_t ostride, LbfgsState *states, int nfits, int m,
+                        double c1, double ftol, hipStream_t stream);
+// The combine, the L-BFGS update and the weights of the next trial point of every
+// vector of a batch whose args.V lies in its state.  polar: parameters (|V_a|, arg V_a)
+// with |V_a| >= rmin (projected steps), arg V_0 fixed at 0 and phases wrapped into
+// [-pi, pi] after each accepted step; the evaluation reads vt.  Otherwise (Re V_a,
+// Im V_a), and the evaluation reads xt.
+hipError_t launch_batch_step(const BatchArgs &args, LbfgsState *states, double c1, double ftol, bool polar, double rmin,
+                             hipStream_t stream);
 
 // Copies n rows of `width` bytes from src (rows src_pitch apart; host or
 // device memory per kind) to dst (rows dst_pitch apart, the bytes past width

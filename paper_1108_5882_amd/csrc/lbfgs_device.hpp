@@ -19,12 +19,12 @@
 //
 // Everything a wave needs sits in its registers: lane i holds parameters i and
 // i + 64, and the history's pairs, newest first, are all loaded at once.  Dot
-// products add their terms in index order (deterministic; a fit from single-precision
-// sums magnifies the last bit of a trial point).  Bound by latency: one round of
-// loads for the state, one for the history, about 20 dot products.  24
-// fits of up to 48 waves: 9.3 us per update, 32 starts of 8 waves 6.2 us; 13.2 and
-// 14.1 us when a block of 128 threads walked the
-// history in memory with three barriers per dot product.
+// products add their terms in index order (deterministic; a fit from
+// single-precision sums magnifies the last bit of a trial point).  Bound by
+// latency: one round of loads for the state, one for the history, about 20 dot
+// products.  24 fits of up to 48 waves: 9.3 us per update, 32 starts of 8 waves
+// 6.2 us; 13.2 and 14.1 us when a block of 128 threads walked the history in
+// memory with three barriers per dot product.
 //
 // Polar mode (the other representation Section 4 discusses): parameters
 // (|V_a|, arg V_a) per wave.  The gradient in them follows from the one in
@@ -124,42 +124,67 @@ __device__ __forceinline__ void lb_polar_trial(LbVec &xt, LbVec &vt, double rmin
     }
 }
 
+// A fit's state in the registers of one wave.
+struct LbRegs {
+    LbVec xt, x, g, d, vt;
+    LbVec S[kLbfgsHist], Y[kLbfgsHist];               // the history, newest pair first
+    double rho[kLbfgsHist];
+    double f, alpha, gtd;
+    int status, phase, head, count;
+};
+
+// Loads the state (n parameters) by one whole wave.
+__device__ __forceinline__ void lbfgs_load(LbRegs &r, const LbfgsState *st, int n, bool polar) {
+    constexpr int m = kLbfgsHist;
+    const int lane = threadIdx.x & 63;
+    r.xt = lb_load(st->xt, n, lane);
+    r.x = lb_load(st->x, n, lane);
+    r.g = lb_load(st->g, n, lane);
+    r.d = lb_load(st->d, n, lane);
+    r.vt = LbVec{};
+    if (polar) r.vt = lb_load(st->vt, n, lane);
+    r.status = st->status;
+    r.phase = st->phase;
+    r.head = st->head;
+    r.count = st->count;
+    r.f = st->f;
+    r.alpha = st->alpha;
+    r.gtd = st->gtd;
+#pragma unroll
+    for (int t = 0; t < m; ++t) {
+        const int i = (r.head - 1 - t + 2 * m) % m;
+        r.S[t] = lb_load(st->S[i], n, lane);
+        r.Y[t] = lb_load(st->Y[i], n, lane);
+        r.rho[t] = st->rho[i];
+    }
+}
+
 // Advances the fit's state after its trial point was evaluated: ft its NLL, gt its
-// gradient in (Re V_a, Im V_a) (n values).  Called by one whole wave, with 64 kLbfgsPer
-// doubles of LDS of its own (prod).  Returns the
-// vector the next evaluation reads (the trial point, or the V it stands for).
-__device__ __forceinline__ LbVec lbfgs_advance(LbfgsState *st, int n, double ft, const double *gt_in, double c1,
+// gradient in (Re V_a, Im V_a).  Called by the wave that holds the state, with 64
+// kLbfgsPer doubles of LDS of its own (prod).  Returns the vector the next
+// evaluation reads (the trial point, or the V it stands for).
+__device__ __forceinline__ LbVec lbfgs_advance(LbfgsState *st, LbRegs &r, int n, double ft, LbVec gt, double c1,
                                                double ftol, bool polar, double rmin, double *prod) {
     constexpr int m = kLbfgsHist;
     const int lane = threadIdx.x & 63;
     const bool odd = lane & 1;
-    LbVec gt = lb_load(gt_in, n, lane);
-    LbVec xt = lb_load(st->xt, n, lane), x = lb_load(st->x, n, lane), g = lb_load(st->g, n, lane),
-          d = lb_load(st->d, n, lane), vt{};
-    if (polar) vt = lb_load(st->vt, n, lane);
-    const int status = st->status, phase = st->phase, head = st->head;
-    int count = st->count;
-    double f = st->f, alpha = st->alpha, gtd = st->gtd;
-    if (status != 0) return polar ? vt : xt;
-    // the history, newest pair first
-    LbVec S[m], Y[m];
-    double rho[m];
-#pragma unroll
-    for (int t = 0; t < m; ++t) {
-        const int i = (head - 1 - t + 2 * m) % m;
-        S[t] = lb_load(st->S[i], n, lane);
-        Y[t] = lb_load(st->Y[i], n, lane);
-        rho[t] = st->rho[i];
-    }
+    LbVec &xt = r.xt, &x = r.x, &g = r.g, &d = r.d, &vt = r.vt;
+    LbVec(&S)[m] = r.S;
+    LbVec(&Y)[m] = r.Y;
+    double(&rho)[m] = r.rho;
+    double &f = r.f, &alpha = r.alpha, &gtd = r.gtd;
+    int &count = r.count;
+    const int phase = r.phase, head = r.head;
+    if (r.status != 0) return polar ? vt : xt;
     if (polar) {
         // gradient in (|V_a|, arg V_a) at the trial point (arg V_0 held fixed)
         const LbVec xo = lb_pair(xt), go = lb_pair(gt);
 #pragma unroll
         for (int u = 0; u < kLbfgsPer; ++u) {
-            const double r = odd ? xo.e[u] : xt.e[u], ph = odd ? xt.e[u] : xo.e[u];
+            const double mag = odd ? xo.e[u] : xt.e[u], ph = odd ? xt.e[u] : xo.e[u];
             const double gre = odd ? go.e[u] : gt.e[u], gim = odd ? gt.e[u] : go.e[u];
             const double c = cos(ph), sn = sin(ph);
-            gt.e[u] = odd ? (lane == 1 && u == 0 ? 0.0 : r * fma(c, gim, -(sn * gre))) : fma(c, gre, sn * gim);
+            gt.e[u] = odd ? (lane == 1 && u == 0 ? 0.0 : mag * fma(c, gim, -(sn * gre))) : fma(c, gre, sn * gim);
         }
     }
 
