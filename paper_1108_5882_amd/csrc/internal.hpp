@@ -178,13 +178,19 @@ struct MultiFit {
     int32_t item_data0, item_data1, item_mc0, item_mc1;   // item ranges of the two samples
     int32_t pad_;
     double n_gen;
-    const double *V;           // trial vector (2k doubles) the evaluation reads
+    const double *V;           // trial vector (2k doubles, 16-byte aligned) the evaluation reads
 };
 
+// A range of tiles of one sample of one fit, with all that streaming it needs.
 struct MultiItem {
-    int32_t fit;
-    int32_t seg;               // 0 data, 1 MC
+    const float *A;            // the sample's rows
+    const float *w;            // MC weights or nullptr
+    const double *V;           // the fit's trial vector
+    int64_t n;                 // rows of the sample
     int64_t t0, t1;            // tile range within the sample
+    int32_t ld, k;
+    int32_t seg;               // 0 data, 1 MC
+    int32_t pad_;
 };
 
 struct MultiArgs {
@@ -210,10 +216,10 @@ int64_t multi_layout_ld(int k);              // -1 if k is too large
 bool multi_ld_supported(int64_t ld);
 int multi_rows_per_tile(int64_t ld);         // rows one wave covers per tile
 hipError_t launch_multi_eval(const MultiArgs &args, int blocks, hipStream_t stream);
-// One L-BFGS update per fit in (Re V_a, Im V_a): fit f has 2 fits[f].k parameters
-// and its result [nll, grad] at out + f * ostride; the next evaluation reads xt.
-hipError_t launch_lbfgs(const MultiFit *fits, const double *out, int64_t ostride, LbfgsState *states, int nfits, int m,
-                        double c1, double ftol, hipStream_t stream);
+// The evaluation, then one L-BFGS update per fit in (Re V_a, Im V_a); the next
+// evaluation reads xt.
+hipError_t launch_multi_step(const MultiArgs &args, int blocks, LbfgsState *states, int m, double c1, double ftol,
+                             hipStream_t stream);
 // The combine, the L-BFGS update and the weights of the next trial point of every
 // vector of a batch whose args.V lies in its state.  polar: parameters (|V_a|, arg V_a)
 // with |V_a| >= rmin (projected steps), arg V_0 fixed at 0 and phases wrapped into

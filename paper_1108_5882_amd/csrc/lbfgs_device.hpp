@@ -22,9 +22,9 @@
 // products add their terms in index order (deterministic; a fit from
 // single-precision sums magnifies the last bit of a trial point).  Bound by
 // latency: one round of loads for the state, one for the history, about 20 dot
-// products.  24 fits of up to 48 waves: 9.3 us per update, 32 starts of 8 waves
-// 6.2 us; 13.2 and 14.1 us when a block of 128 threads walked the history in
-// memory with three barriers per dot product.
+// products.  As launches of their own: 24 fits of up to 48 waves 9.3 us per update,
+// 32 starts of 8 waves 6.2 us; 13.2 and 14.1 us when a block of 128 threads walked
+// the history in memory with three barriers per dot product.
 //
 // Polar mode (the other representation Section 4 discusses): parameters
 // (|V_a|, arg V_a) per wave.  The gradient in them follows from the one in

@@ -95,7 +95,9 @@ pwa_status build_items(pwa_multi *m) {
             const int64_t n = seg ? ft.n_mc : ft.n_data;
             const int64_t tiles = (n + rpt - 1) / rpt;
             const int first = (int)items.size();
-            for (int64_t t = 0; t < tiles; t += tpi) items.push_back(MultiItem{f, seg, t, std::min(t + tpi, tiles)});
+            for (int64_t t = 0; t < tiles; t += tpi)
+                items.push_back(MultiItem{seg ? ft.A_mc : ft.A_data, seg ? ft.w_mc : nullptr, ft.V, n, t,
+                                          std::min(t + tpi, tiles), (int32_t)ft.ld, ft.k, seg, 0});
             (seg ? ft.item_mc0 : ft.item_data0) = first;
             (seg ? ft.item_mc1 : ft.item_data1) = (int)items.size();
         }
@@ -136,9 +138,7 @@ int grid_of(const pwa_multi *m) {
 pwa_status ensure_graph(pwa_multi *m) {
     if (m->exec) return PWA_OK;
     M_HIP(m, hipStreamBeginCapture(m->stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-    hipError_t e = launch_multi_eval(args_of(m), grid_of(m), m->stream);
-    if (e == hipSuccess)
-        e = launch_lbfgs(m->d_fits, m->d_out, kMultiOut, m->d_states, m->nfits, m->m, m->c1, m->ftol, m->stream);
+    hipError_t e = launch_multi_step(args_of(m), grid_of(m), m->d_states, m->m, m->c1, m->ftol, m->stream);
     hipGraph_t g = nullptr;
     hipError_t e2 = hipStreamEndCapture(m->stream, &g);
     if (e != hipSuccess || e2 != hipSuccess) {

@@ -8,12 +8,13 @@
 // of the item with the fused single-V arithmetic (FP32 storage, FP64 z, I,
 // z/I and sums) and write one FP64 partial per item.  Because each item has
 // its own slot, results do not depend on which block took which item.  A
-// combine kernel adds each fit's item partials in item order and forms NLL
-// and gradient; a minimiser kernel then advances each fit's L-BFGS state.
-// The three kernels are captured once in a HIP graph and replayed per step.
+// combine kernel adds each fit's item partials in item order, forms NLL and
+// gradient and advances the fit's L-BFGS state.  The two kernels are captured
+// once in a HIP graph and replayed per step.
 //
 // Row widths differ between fits (K from 4 to 48): each item carries its
 // width and the block dispatches to the compiled tile shape for it.
+#include "lbfgs_device.hpp"
 #include "nll_stream_impl.hpp"
 
 namespace pwa {
@@ -69,21 +70,23 @@ __device__ __forceinline__ void load_chunked(Stage<float, L, C, U, SEG> &st, con
     }
 }
 
-template <int L, int C, int U, int SEG, bool CH = false>
-__device__ __forceinline__ void multi_item(const MultiItem &it, const MultiFit &fit, double *slot, double *red) {
+// grab() asks for the block's next item and is called once the first rows are on
+// their way; fetch() follows the barrier that publishes the answer.
+template <int L, int C, int U, int SEG, bool CH = false, typename Grab, typename Fetch>
+__device__ __forceinline__ void multi_item(const MultiItem &it, double *slot, double *red, Grab grab, Fetch fetch) {
     constexpr int SLOT = 2 * C + 1;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int g = lane / L, j = lane % L;
-    const float *A = SEG ? fit.A_mc : fit.A_data;
-    const float *W = SEG ? fit.w_mc : nullptr;
-    const int64_t n = SEG ? fit.n_mc : fit.n_data;
-    const double *V = fit.V;
-    double vr[C], vi[C];
+    const float *A = it.A;
+    const float *W = SEG ? it.w : nullptr;
+    const int64_t n = it.n;
+    // waves past k read wave 0 (a load under a mask would be waited for before the rows are asked for)
+    typedef const stream_detail::d2v __attribute__((address_space(1))) *gpv;
+    stream_detail::d2v v[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const int a = wave_of<L, C, CH>(j, c);
-        vr[c] = a < fit.k ? V[2 * a] : 0.0;
-        vi[c] = a < fit.k ? V[2 * a + 1] : 0.0;
+        v[c] = *((gpv)it.V + (a < it.k ? a : 0));
     }
     // row stride L * C (the item's width selected this shape)
     auto ld_stage = [&](Stage<float, L, C, U, SEG> &st, int64_t tt) {
@@ -100,13 +103,23 @@ __device__ __forceinline__ void multi_item(const MultiItem &it, const MultiFit &
     constexpr int ROWS = (64 / L) * U;
     const int64_t nfull = n / ROWS;   // tiles whose rows all exist
     int64_t t = it.t0 + wid;
+    Stage<float, L, C, U, SEG> s0, s1;
+    // the same two-stage schedule as the single-fit pass: whole tiles
+    // without clamping or masks while they last, then the clamped loads
+    // (a wave without a tile loads clamped rows it does not use)
+    const bool whole = t + kMW < it.t1 && t + 2 * kMW < nfull;
+    if (whole) ld_full(s0, t);
+    else ld_stage(s0, t);
+    grab();
+    double vr[C], vi[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const bool there = wave_of<L, C, CH>(j, c) < it.k;
+        vr[c] = there ? v[c].x : 0.0;
+        vi[c] = there ? v[c].y : 0.0;
+    }
     if (t < it.t1) {
-        Stage<float, L, C, U, SEG> s0, s1;
-        // the same two-stage schedule as the single-fit pass: whole tiles
-        // without clamping or masks while they last, then the clamped loads
-        if (t + kMW < it.t1 && t + 2 * kMW < nfull) {
-            ld_full(s0, t);
-            stream_detail::fence_sched();
+        if (whole) {
             do {
                 ld_full(s1, t + kMW);
                 stream_detail::fence_sched();
@@ -117,9 +130,6 @@ __device__ __forceinline__ void multi_item(const MultiItem &it, const MultiFit &
                 s1.template compute<false>(n, t, g, vr, vi, acc_t, acc_r, acc_i);
                 t += kMW;
             } while (t + kMW < it.t1 && t + 2 * kMW < nfull);
-        } else {
-            ld_stage(s0, t);
-            stream_detail::fence_sched();
         }
         // s0 holds tile t
         while (t < it.t1) {
@@ -153,6 +163,7 @@ __device__ __forceinline__ void multi_item(const MultiItem &it, const MultiFit &
         }
     }
     __syncthreads();
+    fetch();
     const int ps = 1 + 2 * L * C;
     for (int idx = threadIdx.x; idx < ps; idx += kMT) {
         double s = 0.0;
@@ -176,103 +187,162 @@ __device__ __forceinline__ void multi_item(const MultiItem &it, const MultiFit &
     __syncthreads();
 }
 
-template <int SEG>
-__device__ __forceinline__ void dispatch_item(const MultiItem &it, const MultiFit &fit, double *slot, double *red) {
-    switch (fit.ld) {
-        case 4: multi_item<2, 2, 4, SEG>(it, fit, slot, red); break;
-        case 6: multi_item<2, 3, 2, SEG>(it, fit, slot, red); break;
-        case 8: multi_item<4, 2, 4, SEG>(it, fit, slot, red); break;
-        case 12: multi_item<4, 3, 2, SEG>(it, fit, slot, red); break;
-        case 16: multi_item<8, 2, 4, SEG>(it, fit, slot, red); break;
-        case 24: multi_item<4, 6, 2, SEG, true>(it, fit, slot, red); break;
-        case 32: multi_item<16, 2, 4, SEG>(it, fit, slot, red); break;
-        case 48: multi_item<8, 6, 2, SEG, true>(it, fit, slot, red); break;
-        default: break;
+template <int SEG, typename Grab, typename Fetch>
+__device__ __forceinline__ void dispatch_item(const MultiItem &it, double *slot, double *red, Grab grab, Fetch fetch) {
+    switch (it.ld) {
+        case 4: multi_item<2, 2, 4, SEG>(it, slot, red, grab, fetch); break;
+        case 6: multi_item<2, 3, 2, SEG>(it, slot, red, grab, fetch); break;
+        case 8: multi_item<4, 2, 4, SEG>(it, slot, red, grab, fetch); break;
+        case 12: multi_item<4, 3, 2, SEG>(it, slot, red, grab, fetch); break;
+        case 16: multi_item<8, 2, 4, SEG>(it, slot, red, grab, fetch); break;
+        case 24: multi_item<4, 6, 2, SEG, true>(it, slot, red, grab, fetch); break;
+        case 32: multi_item<16, 2, 4, SEG>(it, slot, red, grab, fetch); break;
+        default: multi_item<8, 6, 2, SEG, true>(it, slot, red, grab, fetch); break;      // 48
     }
 }
 
-__global__ __launch_bounds__(kMT) void multi_stream_kernel(MultiArgs p) {
-    __shared__ int s_item;
+// A block asks for its next item while it streams the current one, and reads that
+// item's descriptor during the current one's reduction.  Registers of the widest
+// rows allow two blocks per compute unit (a few spilled values are read outside the
+// row loops); without the bound one block fits and its waits are bare.
+// Shares of the rows fixed per block, of equal bytes, took 102 us (fewer items, but
+// the blocks differ in speed), four blocks per compute unit with narrower row
+// shapes 115 us.  24 fits, 475 MB of rows: 92 us (5.2 TB/s); 101 us when a block
+// asked after it had finished, read descriptor, fit and V in turn and stood alone.
+__global__ __launch_bounds__(kMT, 2) void multi_stream_kernel(MultiArgs p) {
+    __shared__ int s_next;
     __shared__ double red[kMW * 64 * kRedSlot];
-    for (;;) {
-        if (threadIdx.x == 0) s_item = (int)atomicAdd(p.item_counter, 1u);
-        __syncthreads();
-        const int item = s_item;
-        __syncthreads();
-        if (item >= p.n_items) break;
-        const MultiItem it = p.items[item];
-        const MultiFit fit = p.fits[it.fit];
+    // descriptors through the scalar cache, apart from the rows in flight
+    typedef const MultiItem __attribute__((address_space(4))) *citem;
+    const citem items = (citem)p.items;
+    auto descriptor = [&](int i) {
+        const citem c = items + (i < p.n_items ? i : 0);
+        return MultiItem{c->A, c->w, c->V, c->n, c->t0, c->t1, c->ld, c->k, c->seg, 0};
+    };
+    int item = blockIdx.x;                             // the grid has at most n_items blocks
+    if (item >= p.n_items) return;                     // no items at all
+    MultiItem it = descriptor(item);
+    while (item < p.n_items) {
         double *slot = p.partials + (int64_t)item * kMultiSlot;
+        int next = 0;
+        MultiItem ahead;
+        auto grab = [&]() {
+            if (threadIdx.x == 0) s_next = (int)(gridDim.x + atomicAdd(p.item_counter, 1u));
+        };
+        auto fetch = [&]() {
+            next = __builtin_amdgcn_readfirstlane(s_next);
+            ahead = descriptor(next);
+        };
         // MC rows with weights (segment kind 1) or unit weights (2): a
         // compile-time choice, so the row loop holds no branch on it
         if (it.seg == 0)
-            dispatch_item<0>(it, fit, slot, red);
-        else if (fit.w_mc)
-            dispatch_item<1>(it, fit, slot, red);
+            dispatch_item<0>(it, slot, red, grab, fetch);
+        else if (it.w)
+            dispatch_item<1>(it, slot, red, grab, fetch);
         else
-            dispatch_item<2>(it, fit, slot, red);
+            dispatch_item<2>(it, slot, red, grab, fetch);
+        item = next;
+        it = ahead;
     }
 }
 
 // One block per fit: adds the fit's item partials and forms NLL and gradient
-// (Eq. 2 form), written to out[fit][2k + 2].  Slice s of a column adds items
-// i0 + s, i0 + s + kSlices, ... (independent loads, several in flight); the
-// slices are then added in slice order, so the result does not depend on
-// which block evaluated which item.
-constexpr int kCombineThreads = 1024;
+// (Eq. 2 form).  Slice s of a column adds items i0 + s, i0 + s + kSlices, ...; the
+// slices are then added in slice order, so the result does not depend on which
+// block evaluated which item.  A thread's sums (up to kSums of both samples) go
+// through their items side by side.
+//
+// With STEP the first wave then advances the fit's L-BFGS state, loaded ahead of the
+// partials; otherwise the result goes to out[fit][2k + 2].  Bound by latency: 24
+// fits of up to 48 waves 16.5 us; the sums (7.6) and the
+// update (9.3) were two launches, some 4 us apart.
+constexpr int kCombineThreads = 512;
 constexpr int kSlices = 16;
 
-__global__ __launch_bounds__(kCombineThreads) void multi_combine_kernel(MultiArgs p) {
+template <bool STEP>
+__global__ __launch_bounds__(kCombineThreads) void multi_combine_kernel(MultiArgs p, LbfgsState *states, double c1,
+                                                                        double ftol) {
+    constexpr int kSums = (kSlices * 2 * (1 + 2 * kMultiMaxLd) + kCombineThreads - 1) / kCombineThreads;
     __shared__ double part[kSlices][2][1 + 2 * kMultiMaxLd];
     __shared__ double tot[2][1 + 2 * kMultiMaxLd];
-    __shared__ double s_c;
+    __shared__ double prod[64 * kLbfgsPer];
     const int f = blockIdx.x, tid = threadIdx.x;
     const MultiFit fit = p.fits[f];
     const int k = fit.k, ps = 1 + 2 * (int)fit.ld;
-    for (int idx = tid; idx < kSlices * 2 * ps; idx += kCombineThreads) {
-        const int sl = idx / (2 * ps), rem = idx % (2 * ps);
-        const int sg = rem / ps, cc = rem % ps;
-        const int i0 = sg ? fit.item_mc0 : fit.item_data0;
-        const int i1 = sg ? fit.item_mc1 : fit.item_data1;
-        double s = 0.0;
-#pragma unroll 4
-        for (int i = i0 + sl; i < i1; i += kSlices) s += p.partials[(int64_t)i * kMultiSlot + cc];
-        part[sl][sg][cc] = s;
+    LbRegs r;
+    if (STEP && tid < 64) lbfgs_load(r, states + f, 2 * k, false);
+    const int n0 = fit.item_data1 - fit.item_data0, n1 = fit.item_mc1 - fit.item_mc0;
+    double s[kSums];
+    const double *src[kSums];
+    int left[kSums];                                   // items of the sum not yet added
+#pragma unroll
+    for (int u = 0; u < kSums; ++u) {
+        const int idx = tid + u * kCombineThreads, sl = idx / (2 * ps), rem = idx - sl * 2 * ps;
+        const int sg = rem >= ps;
+        const int n = sl >= kSlices ? 0 : (sg ? n1 : n0) - sl;
+        s[u] = 0.0;
+        left[u] = n > 0 ? (n + kSlices - 1) / kSlices : 0;
+        // a sum without items reads the first partial
+        src[u] = p.partials +
+                 (left[u] ? (int64_t)((sg ? fit.item_mc0 : fit.item_data0) + sl) * kMultiSlot + rem - sg * ps : 0);
+    }
+    const int trips = (max(n0, n1) + kSlices - 1) / kSlices;
+    for (int i = 0; i < trips; ++i) {
+        double x[kSums];
+#pragma unroll
+        for (int u = 0; u < kSums; ++u) x[u] = *src[u];
+#pragma unroll
+        for (int u = 0; u < kSums; ++u) {
+            if (left[u] > 0) s[u] += x[u];
+            if (--left[u] > 0) src[u] += kSlices * kMultiSlot;     // past its last item a sum reads that one again
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kSums; ++u) {
+        const int idx = tid + u * kCombineThreads, sl = idx / (2 * ps), rem = idx - sl * 2 * ps;
+        if (sl < kSlices) part[sl][rem >= ps][rem >= ps ? rem - ps : rem] = s[u];
     }
     __syncthreads();
     for (int idx = tid; idx < 2 * ps; idx += kCombineThreads) {
-        const int sg = idx / ps, cc = idx % ps;
-        double s = 0.0;
-        for (int sl = 0; sl < kSlices; ++sl) s += part[sl][sg][cc];
-        tot[sg][cc] = s;
+        const int sg = idx >= ps, cc = idx - sg * ps;
+        double t = 0.0;
+#pragma unroll
+        for (int sl = 0; sl < kSlices; ++sl) t += part[sl][sg][cc];
+        tot[sg][cc] = t;
     }
     __syncthreads();
-    double *out = p.out + (int64_t)f * kMultiOut;
-    if (tid == 0) {
-        const double nd = (double)fit.n_data;
-        const double sum_log = tot[0][0] * EventMath<float>::kLogScale;
-        const double s_raw = tot[1][0];
-        double nll, c;
-        unsigned flags = 0;
-        if (nd == 0.0) {
-            nll = 0.0;
-            c = 0.0;
-        } else {
-            const double S = s_raw / fit.n_gen;
-            nll = -sum_log + nd * log(S);
-            c = nd / s_raw;
-            if (!isfinite(nll) || !(S > 0.0)) {
-                nll = INFINITY;
-                flags = 1;
-            }
-        }
-        out[0] = nll;
-        out[1 + 2 * k] = (double)flags;
-        s_c = c;
-    }
-    __syncthreads();
-    for (int i = tid; i < 2 * k; i += kCombineThreads) out[1 + i] = 2.0 * (-tot[0][1 + i] + s_c * tot[1][1 + i]);
     if (f == 0 && tid == 0) *p.item_counter = 0u;      // ready for the next launch
+    if (tid >= 64) return;
+    const double nd = (double)fit.n_data;
+    const double sum_log = tot[0][0] * EventMath<float>::kLogScale;
+    const double s_raw = tot[1][0];
+    double nll = 0.0, c = 0.0;
+    unsigned flags = 0;
+    if (nd != 0.0) {
+        const double S = s_raw / fit.n_gen;
+        nll = -sum_log + nd * log(S);
+        c = nd / s_raw;
+        if (!isfinite(nll) || !(S > 0.0)) {
+            nll = INFINITY;
+            flags = 1;
+        }
+    }
+    LbVec g;
+#pragma unroll
+    for (int u = 0; u < kLbfgsPer; ++u) {
+        const int i = tid + 64 * u;
+        g.e[u] = i < 2 * k ? 2.0 * (-tot[0][1 + i] + c * tot[1][1 + i]) : 0.0;
+    }
+    if constexpr (STEP) {
+        lbfgs_advance(states + f, r, 2 * k, nll, g, c1, ftol, false, 0.0, prod);
+    } else {
+        double *out = p.out + (int64_t)f * kMultiOut;
+        lb_store(out + 1, g, 2 * k, tid);
+        if (tid == 0) {
+            out[0] = nll;
+            out[1 + 2 * k] = (double)flags;
+        }
+    }
 }
 
 }  // namespace
@@ -281,7 +351,19 @@ hipError_t launch_multi_eval(const MultiArgs &args, int blocks, hipStream_t stre
     hipLaunchKernelGGL(multi_stream_kernel, dim3(blocks), dim3(kMT), 0, stream, args);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(multi_combine_kernel, dim3(args.n_fits), dim3(kCombineThreads), 0, stream, args);
+    hipLaunchKernelGGL(multi_combine_kernel<false>, dim3(args.n_fits), dim3(kCombineThreads), 0, stream, args, nullptr,
+                       0.0, 0.0);
+    return hipGetLastError();
+}
+
+hipError_t launch_multi_step(const MultiArgs &args, int blocks, LbfgsState *states, int m, double c1, double ftol,
+                             hipStream_t stream) {
+    if (m != kLbfgsHist) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(multi_stream_kernel, dim3(blocks), dim3(kMT), 0, stream, args);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(multi_combine_kernel<true>, dim3(args.n_fits), dim3(kCombineThreads), 0, stream, args, states, c1,
+                       ftol);
     return hipGetLastError();
 }
 
