@@ -248,8 +248,8 @@ typedef enum { PWA_PARAM_CARTESIAN = 0, PWA_PARAM_POLAR = 1 } pwa_param;
  * recomputed exactly: NLL and gradient within 1e-6 of the oracle's) and
  * advances one device L-BFGS state per vector (two-loop recursion, history 8,
  * Armijo backtracking) in the parameters `param` selects (rmin: the polar
- * magnitude bound, >= 0; ignored for PWA_PARAM_CARTESIAN); the iteration is
- * captured in a HIP graph and replayed `iters` times.  Outputs (host, any may
+ * magnitude bound, >= 0; ignored for PWA_PARAM_CARTESIAN); an iteration is
+ * three launches, and nothing crosses the bus between them.  Outputs (host, any may
  * be NULL): V nv x 2k accepted points as (Re V_a, Im V_a) (in polar form with
  * V_0 real and non-negative), nll[nv] their NLL, status[nv] (0 running,
  * 1 converged, 2 step underflow), avg_ms time per iteration.  FP32 contexts,
@@ -380,8 +380,8 @@ const char *pwa_kin_last_error(const pwa_kin *kc);
  * points and with many models).  Every fit has its own samples and its own
  * production vector; one minimiser iteration of all fits is one persistent
  * evaluation launch over the rows of every fit (uneven sizes balanced by a
- * work-item queue), a per-fit combine, and one L-BFGS update per fit on the
- * device, captured in a HIP graph and replayed per step.  FP32 amplitudes, the
+ * work-item queue) and one launch that adds each fit's partials and advances its
+ * L-BFGS state on the device.  FP32 amplitudes, the
  * Eq. 2 form, streamed MC.
  * ------------------------------------------------------------------------ */
 typedef struct pwa_multi pwa_multi;
@@ -415,9 +415,9 @@ pwa_status pwa_multi_eval(pwa_multi *m, const double *V, double *nll, double *gr
 /* Restart every minimiser at V0 (concatenated). */
 pwa_status pwa_multi_reset(pwa_multi *m, const double *V0);
 
-/* Replay `steps` minimiser iterations (the captured graph).  Each replay
- * evaluates every fit's trial point and advances its L-BFGS state (Armijo
- * backtracking; history 8).  avg_ms (optional): HIP-event time per replay. */
+/* Run `steps` minimiser iterations.  Each evaluates every fit's trial point and
+ * advances its L-BFGS state (Armijo backtracking; history 8).  avg_ms (optional):
+ * HIP-event time per iteration. */
 pwa_status pwa_multi_step(pwa_multi *m, int32_t steps, double *avg_ms);
 
 /* Current accepted points (concatenated), NLL values, status (0 running,
@@ -427,7 +427,7 @@ pwa_status pwa_multi_get(pwa_multi *m, double *V, double *nll, int32_t *status, 
 
 /* Autotuner of the persistent launch: times the evaluation of all fits for
  * work items of 64 KB .. 4 MB of rows and 1 .. 16 blocks per compute unit,
- * `reps` launches each, keeps the fastest (and rebuilds the graph). */
+ * `reps` launches each, keeps the fastest. */
 pwa_status pwa_multi_autotune(pwa_multi *m, int32_t reps, int64_t *item_bytes, int32_t *blocks_per_cu,
                               double *best_ms);
 

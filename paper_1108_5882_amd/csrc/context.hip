@@ -103,6 +103,10 @@ struct pwa_ctx {
     size_t planes_cap[2] = {0, 0};
     bool planes_valid[2] = {false, false};
     float *b_rnorm = nullptr;
+    void *f_states = nullptr;        // a batch fit's L-BFGS states
+    size_t f_cap = 0;
+    char *f_host = nullptr;          // and its starts and results, mapped host memory
+    size_t f_host_cap = 0;
     void *b_flags = nullptr;
     size_t flags_cap = 0;
     // Hessian: block partials, T, V, H and a status word
@@ -657,14 +661,32 @@ pwa_status pwa_batch_fit(pwa_ctx *ctx, int32_t nv, const double *V0, int32_t ite
     pwa_status st = batch_setup(ctx, nv, a, &gpad);
     if (st != PWA_OK) return st;
     if (a.n[0] > 0 && (st = refine_setup(ctx, nv, a, true)) != PWA_OK) return st;
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    PWA_HIP(ctx, hipStreamIsCapturing(ctx->stream, &capturing), "hipStreamIsCapturing");
+    if (capturing != hipStreamCaptureStatusNone)
+        return fail(ctx, PWA_E_HIP, "batched fit: the context's stream is capturing");
+    if ((st = grow(ctx, &ctx->f_states, &ctx->f_cap, sizeof(LbfgsState) * (size_t)nv, "hipMalloc(states)")) != PWA_OK)
+        return st;
+    const size_t host_bytes = (sizeof(FitStart) + sizeof(FitResult)) * (size_t)nv;
+    if (ctx->f_host_cap < host_bytes) {
+        if (ctx->f_host) (void)hipHostFree(ctx->f_host);
+        ctx->f_host = nullptr;
+        ctx->f_host_cap = 0;
+        PWA_HIP(ctx, hipHostMalloc(&ctx->f_host, host_bytes, hipHostMallocMapped | hipHostMallocCoherent),
+                "hipHostMalloc(fits)");
+        ctx->f_host_cap = host_bytes;
+    }
     // L-BFGS states: the matrix-core pass reads each vector's trial point in place
     // (xt, or in polar form the V it stands for, vt)
-    std::vector<LbfgsState> hs(nv);
+    LbfgsState *states = static_cast<LbfgsState *>(ctx->f_states);
+    FitStart *start = reinterpret_cast<FitStart *>(ctx->f_host);
+    FitResult *result = reinterpret_cast<FitResult *>(start + nv);
     for (int v = 0; v < nv; ++v) {
-        std::memset(&hs[v], 0, sizeof(LbfgsState));
+        FitStart &s = start[v];
+        std::memset(&s, 0, sizeof s);
         const double *v0 = V0 + (size_t)v * 2 * k;
         if (!polar) {
-            for (int i = 0; i < 2 * k; ++i) hs[v].xt[i] = v0[i];
+            std::copy(v0, v0 + 2 * k, s.xt);
             continue;
         }
         // polar start: the global phase that makes V_0 real and non-negative, then
@@ -673,69 +695,58 @@ pwa_status pwa_batch_fit(pwa_ctx *ctx, int32_t nv, const double *V0, int32_t ite
         for (int b = 0; b < k; ++b) {
             const double r = std::max(std::hypot(v0[2 * b], v0[2 * b + 1]), rmin);
             const double ph = b == 0 ? 0.0 : std::remainder(std::atan2(v0[2 * b + 1], v0[2 * b]) - ph0, 2.0 * M_PI);
-            hs[v].xt[2 * b] = r;
-            hs[v].xt[2 * b + 1] = ph;
-            hs[v].vt[2 * b] = r * std::cos(ph);
-            hs[v].vt[2 * b + 1] = r * std::sin(ph);
+            s.xt[2 * b] = r;
+            s.xt[2 * b + 1] = ph;
+            s.vt[2 * b] = r * std::cos(ph);
+            s.vt[2 * b + 1] = r * std::sin(ph);
         }
     }
-    LbfgsState *d_states = nullptr;
-    PWA_HIP(ctx, hipMalloc(&d_states, sizeof(LbfgsState) * nv), "hipMalloc(states)");
-    hipError_t e = hipMemcpyAsync(d_states, hs.data(), sizeof(LbfgsState) * nv, hipMemcpyHostToDevice, ctx->stream);
-    a.V = polar ? d_states[0].vt : d_states[0].xt;
+    a.V = polar ? states[0].vt : states[0].xt;
     a.vstride = sizeof(LbfgsState) / sizeof(double);
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    if (e == hipSuccess) e = hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) {
-        // the split-3 pass: matrix-core sums with small coherent sums flagged, their
-        // exact recomputation, then the combine, one L-BFGS update per vector and the
-        // next weights
-        const bool refine = a.n[0] > 0;
-        hipError_t ec = launch_batch(a, refine, ctx->stream);
-        if (ec == hipSuccess && refine) ec = launch_batch_refine(a, ctx->stream);
-        if (ec == hipSuccess) ec = launch_batch_step(a, d_states, 1e-4, 1e-12, polar, rmin, ctx->stream);
-        e = hipStreamEndCapture(ctx->stream, &graph);
-        if (ec != hipSuccess) e = ec;
-    }
-    if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
     hipEvent_t e0 = nullptr, e1 = nullptr;
+    hipError_t e = launch_fit_start(states, start, nv, ctx->stream);
     if (e == hipSuccess && avg_ms) e = hipEventCreate(&e0);
     if (e == hipSuccess && avg_ms) e = hipEventCreate(&e1);
     if (e == hipSuccess && iters > 0) e = launch_batch_weights(a, ctx->stream);
     if (e == hipSuccess && avg_ms) e = hipEventRecord(e0, ctx->stream);
-    for (int it = 0; it < iters && e == hipSuccess; ++it) e = hipGraphLaunch(exec, ctx->stream);
+    // the split-3 pass: matrix-core sums with small coherent sums flagged, their
+    // exact recomputation, then the combine, one L-BFGS update per vector and the
+    // next weights.  Plain launches: three per iteration are on their way well before
+    // the device asks for them (32 starts at K = 8, 20 iterations: 610 us per call; 807 us
+    // with a graph captured and instantiated, states allocated, and whole states copied
+    // both ways in each call)
+    const bool refine = a.n[0] > 0;
+    for (int it = 0; it < iters && e == hipSuccess; ++it) {
+        e = launch_batch(a, refine, ctx->stream);
+        if (e == hipSuccess && refine) e = launch_batch_refine(a, ctx->stream);
+        if (e == hipSuccess) e = launch_batch_step(a, states, 1e-4, 1e-12, polar, rmin, ctx->stream);
+    }
     if (e == hipSuccess && avg_ms) e = hipEventRecord(e1, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    if (e == hipSuccess) e = launch_fit_result(states, result, nv, ctx->stream);
+    // the records are free again only when the stream has passed them
+    const hipError_t done = hipStreamSynchronize(ctx->stream);
+    if (e == hipSuccess) e = done;
     if (e == hipSuccess && avg_ms) {
         float ms = 0.f;
         e = hipEventElapsedTime(&ms, e0, e1);
         *avg_ms = iters ? ms / iters : 0.0;
     }
-    if (e == hipSuccess)
-        e = hipMemcpy(hs.data(), d_states, sizeof(LbfgsState) * nv, hipMemcpyDeviceToHost);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
-    if (exec) (void)hipGraphExecDestroy(exec);
-    if (graph) (void)hipGraphDestroy(graph);
-    (void)hipFree(d_states);
     if (e != hipSuccess) return hip_fail(ctx, e, "batched fit");
     for (int v = 0; v < nv; ++v) {
-        const bool started = hs[v].phase != 0;
-        const double *p = started ? hs[v].x : hs[v].xt;
-        if (V && !polar)
-            for (int i = 0; i < 2 * k; ++i) V[(size_t)v * 2 * k + i] = p[i];
+        const FitResult &r = result[v];
+        if (V && !polar) std::copy(r.x, r.x + 2 * k, V + (size_t)v * 2 * k);
         if (V && polar)
             for (int b = 0; b < k; ++b) {
-                V[(size_t)v * 2 * k + 2 * b] = p[2 * b] * std::cos(p[2 * b + 1]);
-                V[(size_t)v * 2 * k + 2 * b + 1] = p[2 * b] * std::sin(p[2 * b + 1]);
+                V[(size_t)v * 2 * k + 2 * b] = r.x[2 * b] * std::cos(r.x[2 * b + 1]);
+                V[(size_t)v * 2 * k + 2 * b + 1] = r.x[2 * b] * std::sin(r.x[2 * b + 1]);
             }
-        if (nll) nll[v] = started ? hs[v].f : NAN;
-        if (status) status[v] = hs[v].status;
+        if (nll) nll[v] = r.started ? r.f : NAN;
+        if (status) status[v] = r.status;
     }
     return PWA_OK;
 }
-
 
 pwa_status pwa_create(pwa_ctx **out, int device, pwa_prec prec, void *stream) {
     if (!out) return fail(nullptr, PWA_E_INVAL, "null output pointer");
@@ -805,13 +816,14 @@ pwa_status pwa_destroy(pwa_ctx *ctx) {
     if (ctx->counters) (void)hipFree(ctx->counters);
     if (ctx->gram) (void)hipFree(ctx->gram);
     for (void *b : {ctx->b_wfrag, ctx->b_ascale, ctx->b_vscale, ctx->b_V, ctx->b_partials, ctx->b_out,
-                    (void *)ctx->b_amax, (void *)ctx->b_rnorm, ctx->b_flags, ctx->h_buf, ctx->g_buf, ctx->b_planes[0],
-                    ctx->b_planes[1]})
+                    (void *)ctx->b_amax, (void *)ctx->b_rnorm, ctx->b_flags, ctx->h_buf, ctx->g_buf, ctx->f_states,
+                    ctx->b_planes[0], ctx->b_planes[1]})
         if (b) (void)hipFree(b);
     if (ctx->partials) (void)hipFree(ctx->partials);
     if (ctx->out_dev) (void)hipFree(ctx->out_dev);
     if (ctx->out_host) (void)hipHostFree(ctx->out_host);
     if (ctx->h_host) (void)hipHostFree(ctx->h_host);
+    if (ctx->f_host) (void)hipHostFree(ctx->f_host);
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
     return PWA_OK;

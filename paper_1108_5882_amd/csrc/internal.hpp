@@ -212,6 +212,18 @@ struct LbfgsState {
     int32_t head, count, phase, iter, status, nbacktrack;
 };
 
+// Records of a fit in mapped host memory: its start (the trial point, and in polar
+// form the V it stands for) and its result.
+struct FitStart {
+    double xt[kLbfgsMaxN], vt[kLbfgsMaxN];
+};
+struct FitResult {
+    double x[kLbfgsMaxN], f;
+    int32_t started, status, iter, pad_;
+};
+hipError_t launch_fit_start(LbfgsState *states, const FitStart *start, int nfits, hipStream_t stream);
+hipError_t launch_fit_result(const LbfgsState *states, FitResult *result, int nfits, hipStream_t stream);
+
 int64_t multi_layout_ld(int k);              // -1 if k is too large
 bool multi_ld_supported(int64_t ld);
 int multi_rows_per_tile(int64_t ld);         // rows one wave covers per tile

@@ -1,7 +1,6 @@
 // C ABI of the multi-fit minimiser: staging of every fit's samples, the work
 // item list of the persistent evaluation kernel, the L-BFGS state, and the
-// HIP graph that holds one minimiser iteration (evaluate all fits, combine,
-// advance all fits).
+// launches of a minimiser iteration (evaluate all fits; combine and advance them).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -31,12 +30,13 @@ struct pwa_multi {
     double *d_partials = nullptr;
     double *d_out = nullptr;
     LbfgsState *d_states = nullptr;
+    FitStart *h_start = nullptr;           // mapped host memory, one per fit
+    FitResult *h_result = nullptr;
     int64_t item_bytes = 256 * 1024;       // target bytes of rows per work item
     int blocks_per_cu = 2;
     int m = 8;
     double c1 = 1e-4, ftol = 1e-12;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
+    hipEvent_t ev[2] = {nullptr, nullptr}; // around the steps of a timed call
     std::string err;
 };
 
@@ -74,13 +74,6 @@ struct DevGuard {
     }
 };
 
-void drop_graph(pwa_multi *m) {
-    if (m->exec) (void)hipGraphExecDestroy(m->exec);
-    if (m->graph) (void)hipGraphDestroy(m->graph);
-    m->exec = nullptr;
-    m->graph = nullptr;
-}
-
 // Cuts every fit's samples into work items of about item_bytes of rows.
 pwa_status build_items(pwa_multi *m) {
     const int waves = kStreamThreads / 64;
@@ -115,7 +108,6 @@ pwa_status build_items(pwa_multi *m) {
               "hipMemcpy(items)");
     M_HIP(m, hipMemcpy(m->d_fits, m->fits.data(), sizeof(MultiFit) * m->nfits, hipMemcpyHostToDevice),
           "hipMemcpy(fits)");
-    drop_graph(m);
     return PWA_OK;
 }
 
@@ -135,34 +127,17 @@ int grid_of(const pwa_multi *m) {
     return std::max(1, std::min(m->n_items, m->cu_count * m->blocks_per_cu));
 }
 
-pwa_status ensure_graph(pwa_multi *m) {
-    if (m->exec) return PWA_OK;
-    M_HIP(m, hipStreamBeginCapture(m->stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-    hipError_t e = launch_multi_step(args_of(m), grid_of(m), m->d_states, m->m, m->c1, m->ftol, m->stream);
-    hipGraph_t g = nullptr;
-    hipError_t e2 = hipStreamEndCapture(m->stream, &g);
-    if (e != hipSuccess || e2 != hipSuccess) {
-        if (g) (void)hipGraphDestroy(g);
-        return mfail(m, PWA_E_HIP, "graph capture: %s", hipGetErrorString(e != hipSuccess ? e : e2));
-    }
-    m->graph = g;
-    M_HIP(m, hipGraphInstantiate(&m->exec, m->graph, nullptr, nullptr, 0), "hipGraphInstantiate");
-    return PWA_OK;
-}
-
-// Writes every fit's start vector into its L-BFGS state (phase 0).
+// Writes every fit's start vector into its L-BFGS state (phase 0).  The stream is idle
+// on entry: nothing reads the records of an earlier start.
 pwa_status reset_states(pwa_multi *m, const double *V0) {
-    std::vector<LbfgsState> st(m->nfits);
     size_t off = 0;
     for (int f = 0; f < m->nfits; ++f) {
-        LbfgsState &s = st[f];
-        std::memset(&s, 0, sizeof s);
         const int n = 2 * m->fits[f].k;
-        for (int i = 0; i < n; ++i) s.xt[i] = V0[off + i];
+        std::memset(&m->h_start[f], 0, sizeof(FitStart));
+        std::memcpy(m->h_start[f].xt, V0 + off, sizeof(double) * n);
         off += n;
     }
-    M_HIP(m, hipMemcpy(m->d_states, st.data(), sizeof(LbfgsState) * m->nfits, hipMemcpyHostToDevice),
-          "hipMemcpy(states)");
+    M_HIP(m, launch_fit_start(m->d_states, m->h_start, m->nfits, m->stream), "start launch");
     return PWA_OK;
 }
 
@@ -257,7 +232,11 @@ pwa_status pwa_multi_create(pwa_multi **out, int device, int32_t nfits, const pw
         (e = hipMalloc(&m->d_counter, sizeof(unsigned))) != hipSuccess ||
         (e = hipMemset(m->d_counter, 0, sizeof(unsigned))) != hipSuccess ||
         (e = hipMalloc(&m->d_out, sizeof(double) * kMultiOut * nfits)) != hipSuccess ||
-        (e = hipMalloc(&m->d_states, sizeof(LbfgsState) * nfits)) != hipSuccess) {
+        (e = hipMalloc(&m->d_states, sizeof(LbfgsState) * nfits)) != hipSuccess ||
+        (e = hipHostMalloc(&m->h_start, sizeof(FitStart) * nfits, hipHostMallocMapped | hipHostMallocCoherent)) !=
+            hipSuccess ||
+        (e = hipHostMalloc(&m->h_result, sizeof(FitResult) * nfits, hipHostMallocMapped | hipHostMallocCoherent)) !=
+            hipSuccess) {
         mfail(m, PWA_E_NOMEM, "hipMalloc: %s", hipGetErrorString(e));
         return bail(PWA_E_NOMEM);
     }
@@ -272,11 +251,14 @@ pwa_status pwa_multi_destroy(pwa_multi *m) {
     if (!m) return PWA_OK;
     DevGuard dg(m->device);
     if (m->stream) (void)hipStreamSynchronize(m->stream);
-    drop_graph(m);
     for (void *b : m->rows) (void)hipFree(b);
     for (void *b : {(void *)m->d_fits, (void *)m->d_items, (void *)m->d_counter, (void *)m->d_partials,
                     (void *)m->d_out, (void *)m->d_states})
         if (b) (void)hipFree(b);
+    for (hipEvent_t ev : m->ev)
+        if (ev) (void)hipEventDestroy(ev);
+    if (m->h_start) (void)hipHostFree(m->h_start);
+    if (m->h_result) (void)hipHostFree(m->h_result);
     if (m->own_stream && m->stream) (void)hipStreamDestroy(m->stream);
     delete m;
     return PWA_OK;
@@ -322,44 +304,41 @@ pwa_status pwa_multi_eval(pwa_multi *m, const double *V, double *nll, double *gr
 pwa_status pwa_multi_step(pwa_multi *m, int32_t steps, double *avg_ms) {
     if (!m || steps < 0) return mfail(m, PWA_E_INVAL, "bad arguments");
     DevGuard dg(m->device);
-    pwa_status st = ensure_graph(m);
-    if (st != PWA_OK) return st;
-    hipEvent_t e0 = nullptr, e1 = nullptr;
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    M_HIP(m, hipStreamIsCapturing(m->stream, &capturing), "hipStreamIsCapturing");
+    if (capturing != hipStreamCaptureStatusNone) return mfail(m, PWA_E_HIP, "the stream is capturing");
     if (avg_ms) {
-        M_HIP(m, hipEventCreate(&e0), "hipEventCreate");
-        M_HIP(m, hipEventCreate(&e1), "hipEventCreate");
-        M_HIP(m, hipEventRecord(e0, m->stream), "hipEventRecord");
+        for (hipEvent_t &ev : m->ev)
+            if (!ev) M_HIP(m, hipEventCreate(&ev), "hipEventCreate");
+        M_HIP(m, hipEventRecord(m->ev[0], m->stream), "hipEventRecord");
     }
-    for (int s = 0; s < steps; ++s) M_HIP(m, hipGraphLaunch(m->exec, m->stream), "hipGraphLaunch");
-    if (avg_ms) {
-        M_HIP(m, hipEventRecord(e1, m->stream), "hipEventRecord");
-        M_HIP(m, hipEventSynchronize(e1), "hipEventSynchronize");
-        float ms = 0.f;
-        M_HIP(m, hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime");
-        *avg_ms = steps ? ms / steps : 0.0;
-        (void)hipEventDestroy(e0);
-        (void)hipEventDestroy(e1);
-    }
+    // plain launches: two per step are on their way long before the device asks for
+    // them (24 fits, four steps: 537 us per call, 549 us with replays of a graph of them)
+    for (int s = 0; s < steps; ++s)
+        M_HIP(m, launch_multi_step(args_of(m), grid_of(m), m->d_states, m->m, m->c1, m->ftol, m->stream), "step launch");
+    if (avg_ms) M_HIP(m, hipEventRecord(m->ev[1], m->stream), "hipEventRecord");
     M_HIP(m, hipStreamSynchronize(m->stream), "hipStreamSynchronize");
+    if (avg_ms) {
+        float ms = 0.f;
+        M_HIP(m, hipEventElapsedTime(&ms, m->ev[0], m->ev[1]), "hipEventElapsedTime");
+        *avg_ms = steps ? ms / steps : 0.0;
+    }
     return PWA_OK;
 }
 
 pwa_status pwa_multi_get(pwa_multi *m, double *V, double *nll, int32_t *status, int32_t *iters) {
     if (!m) return mfail(nullptr, PWA_E_INVAL, "null argument");
     DevGuard dg(m->device);
+    M_HIP(m, launch_fit_result(m->d_states, m->h_result, m->nfits, m->stream), "result launch");
     M_HIP(m, hipStreamSynchronize(m->stream), "hipStreamSynchronize");
-    std::vector<LbfgsState> st(m->nfits);
-    M_HIP(m, hipMemcpy(st.data(), m->d_states, sizeof(LbfgsState) * m->nfits, hipMemcpyDeviceToHost),
-          "hipMemcpy(states)");
     size_t off = 0;
     for (int f = 0; f < m->nfits; ++f) {
+        const FitResult &r = m->h_result[f];
         const int n = 2 * m->fits[f].k;
-        // before the first evaluation the accepted point is the start point
-        const bool started = st[f].phase != 0;
-        if (V) for (int i = 0; i < n; ++i) V[off + i] = started ? st[f].x[i] : st[f].xt[i];
-        if (nll) nll[f] = started ? st[f].f : NAN;
-        if (status) status[f] = st[f].status;
-        if (iters) iters[f] = st[f].iter;
+        if (V) std::memcpy(V + off, r.x, sizeof(double) * n);
+        if (nll) nll[f] = r.started ? r.f : NAN;
+        if (status) status[f] = r.status;
+        if (iters) iters[f] = r.iter;
         off += n;
     }
     return PWA_OK;

@@ -9,8 +9,7 @@
 // z/I and sums) and write one FP64 partial per item.  Because each item has
 // its own slot, results do not depend on which block took which item.  A
 // combine kernel adds each fit's item partials in item order, forms NLL and
-// gradient and advances the fit's L-BFGS state.  The two kernels are captured
-// once in a HIP graph and replayed per step.
+// gradient and advances the fit's L-BFGS state: two launches per step.
 //
 // Row widths differ between fits (K from 4 to 48): each item carries its
 // width and the block dispatches to the compiled tile shape for it.
