@@ -273,7 +273,7 @@ pwa_status pwa_layout_ld(pwa_ctx *ctx, int32_t k, int64_t *ld);
  *                     equal the layout width pwa_layout_ld() gives for k
  *   rows_per_stage    U: rows each lane group loads per pipeline stage
  *   blocks_per_cu     grid blocks per compute unit, 1..16 (fewer when the
- *                     rows need fewer) */
+ *                     rows are few) */
 typedef struct {
     int32_t lanes_per_row;
     int32_t complex_per_lane;
@@ -290,7 +290,7 @@ pwa_status pwa_get_stream_cfg(pwa_ctx *ctx, pwa_stream_cfg *cfg);
 pwa_status pwa_set_stream_cfg(pwa_ctx *ctx, const pwa_stream_cfg *cfg);
 
 /* Autotuner: times every compiled configuration of the current layout width
- * (and blocks_per_cu in {2, 3, 4, 6, 8, 12, 16}) on the samples currently set,
+ * (and blocks_per_cu in {1, 2, 3, 4, 6, 8, 16}) on the samples currently set,
  * `reps` evaluations each (the pass over the rows and the combine of its
  * block partials) after one warm-up, keeps the fastest (of those within 1% of
  * it, the one with the fewest blocks per CU, then rows per stage, then lanes

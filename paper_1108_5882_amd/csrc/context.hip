@@ -194,7 +194,8 @@ hipError_t sample_memory(void **p, size_t *cap, size_t bytes) {
 }
 
 void split_blocks(const pwa_ctx *ctx, int64_t n0, int64_t n1, int32_t nb[2]) {
-    stream_grid(ctx->cfg, (int64_t)ctx->cu_count * ctx->cfg.blocks_per_cu, n0, n1, nb);
+    stream_grid(ctx->cfg, (int64_t)ctx->cu_count * ctx->cfg.blocks_per_cu,
+                2 * ctx->ld * (int64_t)elem_bytes(ctx->prec), n0, n1, nb);
 }
 
 // Grows a device scratch buffer to at least `bytes`.
@@ -1136,7 +1137,7 @@ pwa_status pwa_autotune(pwa_ctx *ctx, int32_t reps, pwa_stream_cfg *best, double
     hipEvent_t e0, e1;
     PWA_HIP(ctx, hipEventCreate(&e0), "hipEventCreate");
     PWA_HIP(ctx, hipEventCreate(&e1), "hipEventCreate");
-    static const int kBpc[] = {2, 3, 4, 6, 8, 12, 16};
+    static const int kBpc[] = {1, 2, 3, 4, 6, 8, 16};
     int nvar = 0;
     const StreamCfg *vars = stream_variants(ctx->prec, &nvar);
     std::vector<std::pair<StreamCfg, double>> timed;

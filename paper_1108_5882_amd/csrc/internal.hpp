@@ -67,10 +67,10 @@ StreamCfg stream_default_cfg(pwa_prec prec, int ld);
 // True if (L, C, U) is compiled for the precision.
 bool stream_cfg_available(pwa_prec prec, const StreamCfg &c);
 
-// Grid of one evaluation over n0 data and n1 MC rows: blocks per segment, at
-// most what the rows need and at most `budget` in all, split in proportion to
-// the rows.
-void stream_grid(const StreamCfg &cfg, int64_t budget, int64_t n0, int64_t n1, int32_t nb[2]);
+// Grid of one evaluation over n0 data and n1 MC rows of row_bytes each: blocks per
+// segment, at most what the rows need and at most `budget` in all (fewer when the
+// rows are few), split in proportion to the rows.
+void stream_grid(const StreamCfg &cfg, int64_t budget, int64_t row_bytes, int64_t n0, int64_t n1, int32_t nb[2]);
 
 // Message pwa_last_error(NULL) returns on this thread.
 void set_global_error(const char *msg);

@@ -69,10 +69,14 @@ int stream_layout_ld(pwa_prec prec, int k) {
 
 StreamCfg stream_default_cfg(pwa_prec prec, int ld) {
     // Preference: about 32 B per lane per row (fewer lanes per row means less
-    // redundant per-event work), 64 B per lane per stage, 4 blocks per CU.
+    // redundant per-event work), 64 B per lane per stage, one block per CU: its four
+    // waves keep two stages each in flight, and every further block brings partials
+    // and a ragged end.  256 against 1024 blocks, one evaluation: 20 MB of rows 19.7 /
+    // 25.4 us at K = 16, 19.3 / 22.3 at 23; 60 MB 25.5 / 29.6 and 25.5 / 27.2; 180 MB
+    // 42.4 / 49.8; 720 MB 129.9 / 132.2 (numbers between multiples of the CUs are worse).
     const Table &t = table(prec);
     const int eb = prec == PWA_F32 ? 8 : 16;
-    StreamCfg best{0, 0, 0, 4};
+    StreamCfg best{0, 0, 0, 1};
     int best_score = 1 << 30;
     for (int i = 0; i < t.n; ++i) {
         const StreamCfg &c = t.v[i];
@@ -81,13 +85,21 @@ StreamCfg stream_default_cfg(pwa_prec prec, int ld) {
         const int score = std::abs(row_bytes - 32) * 4 + std::abs(stage_bytes - 64);
         if (score < best_score) {
             best_score = score;
-            best = StreamCfg{c.L, c.C, c.U, 4};
+            best = StreamCfg{c.L, c.C, c.U, 1};
         }
     }
     return best;
 }
 
-void stream_grid(const StreamCfg &cfg, int64_t budget, int64_t n0, int64_t n1, int32_t nb[2]) {
+// A block takes at least kLeastBlockBytes of rows, down to kLeastBlocks of them: with
+// less, its partial costs more than it streams.  128 against 256 blocks: 4 MB of rows
+// 16.2 / 17.3 us at K = 23, 7 MB 16.8 / 17.7, 12 MB 18.3 / 18.3, 20 MB 20.6 / 19.3; at
+// 2 MB 64 blocks take 15.5, 128 15.8, 256 16.5 us.
+constexpr int64_t kLeastBlockBytes = 48 << 10;
+constexpr int64_t kLeastBlocks = 64;
+
+void stream_grid(const StreamCfg &cfg, int64_t budget, int64_t row_bytes, int64_t n0, int64_t n1, int32_t nb[2]) {
+    budget = std::min(budget, std::max(kLeastBlocks, (n0 + n1) * row_bytes / kLeastBlockBytes));
     const int64_t rows_per_block = (int64_t)stream_rows_per_wave(cfg) * (kStreamThreads / 64);
     const int64_t need[2] = {(n0 + rows_per_block - 1) / rows_per_block, (n1 + rows_per_block - 1) / rows_per_block};
     if (need[0] + need[1] <= budget) {

@@ -118,7 +118,7 @@ pwa_status pwa_nll_grad_noalloc(pwa_prec prec, const void *A_data, int64_t n_dat
     a.nd_total = (double)n_data;
     a.extended = extended;
     a.out = out_dev;
-    stream_grid(cfg, cap, a.n[0], a.n[1], a.nb);
+    stream_grid(cfg, cap, ld * (prec == PWA_F32 ? 8 : 16), a.n[0], a.n[1], a.nb);
     int blocks = a.nb[0] + a.nb[1];
     if (blocks == 0) {
         a.nb[0] = 1;     // one block still writes the (trivial) result
