@@ -1037,7 +1037,7 @@ pwa_status pwa_hessian(pwa_ctx *ctx, const double *V, double *H) {
     if (need_mc && (st = ensure_gram(ctx)) != PWA_OK) return st;
     const int blocks = hessian_blocks(ctx->prec, k, ctx->cu_count, nd);
     const size_t n_work = hessian_work_doubles(k, blocks), n_h = 4 * (size_t)k * k + 1;
-    const size_t doubles = n_work + 1;                  // the work buffer, then the status word
+    const size_t doubles = n_work + 1;                  // the work buffer, then the status word and arrival count
     const size_t cap0 = ctx->h_cap;
     if ((st = grow(ctx, &ctx->h_buf, &ctx->h_cap, sizeof(double) * doubles, "hipMalloc(hessian)"))) return st;
     if (ctx->h_cap != cap0 || ctx->hess_layout[0] != k || ctx->hess_layout[1] != blocks) ctx->hess_clean = false;
@@ -1072,10 +1072,10 @@ pwa_status pwa_hessian(pwa_ctx *ctx, const double *V, double *H) {
     const bool clear = !ctx->hess_clean;
     ctx->hess_clean = false;
     hipError_t e = launch_hessian(ctx->prec, ctx->s[0].A, nd, ctx->ld, k, V, M, (double)nd, ctx->extended, work,
-                                  blocks, clear, flag, ctx->h_host_dev, ctx->stream);
+                                  blocks, clear, flag, ctx->h_host_dev, ctx->done_dev, ++ctx->seq, ctx->stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "hessian launch");
     if (ctx->timing) PWA_HIP(ctx, hipEventRecord(e1, ctx->stream), "hipEventRecord");
-    PWA_HIP(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
+    if ((st = wait_result(ctx, ctx->seq)) != PWA_OK) return st;
     ctx->hess_clean = true;
     std::copy(ctx->h_host, ctx->h_host + (n_h - 1), H);
     ctx->last_flags = ctx->h_host[n_h - 1] != 0.0 ? 1u : 0u;
