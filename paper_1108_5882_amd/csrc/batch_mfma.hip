@@ -578,40 +578,77 @@ __global__ __launch_bounds__(kThreads) void batch_refine_kernel(BatchArgs p) {
 // of their wave (event-major rows), then BF16 hi / lo of the unscaled
 // amplitudes transposed (real-column-major, event e at position
 // 8 ((e mod 16) / 4) + (e mod 4) + 4 (e / 16)).  Rows past n and columns past
-// 2k hold zeros.  One thread per (event, pair of real columns).
-__global__ void batch_planes_kernel(const float *A, int64_t n, int64_t ld, int nreal, int K2, int64_t ntiles,
-                                    const float *ascale, unsigned short *out) {
-    const int64_t total = ntiles * kTile * (K2 / 2);
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t eg = idx / (K2 / 2);
-        const int r = 2 * (int)(idx % (K2 / 2));
-        const int64_t t = eg / kTile;
-        const int e = (int)(eg % kTile);
-        float x0 = 0.f, x1 = 0.f;
-        if (eg < n && r < nreal) {
-            x0 = A[2 * eg * ld + r];
-            x1 = A[2 * eg * ld + r + 1];
+// 2k hold zeros.
+//
+// Bound by memory (4 bytes read and 8 written per real column).  A block takes tiles
+// in turn: the rows pass through LDS, the next tile's already on their way, and a
+// thread forms 16 bytes of a hi and a lo plane from 8 values, so that a wave writes
+// whole lines.  LDS rows of K2 + 4 floats keep the reads of 16 columns at 4 event
+// groups on distinct banks.  K = 32, 10^7 rows: 1.8 ms; 6.8 ms when a thread wrote the
+// 2-byte values of one event and column pair, 64 bytes apart in the transposed planes.
+template <int KS>
+__global__ __launch_bounds__(256) void batch_planes_kernel(const float *A, int64_t n, int64_t ld, int nreal,
+                                                           int64_t ntiles, const float *ascale, unsigned short *out) {
+    constexpr int K2 = 32 * KS, ST = K2 + 4, PER = kTile * K2 / 2 / 256;
+    typedef unsigned short us8 __attribute__((ext_vector_type(8)));
+    typedef float f2r __attribute__((ext_vector_type(2)));
+    typedef float f4r __attribute__((ext_vector_type(4)));
+    __shared__ __attribute__((aligned(16))) float rows[kTile * ST];
+    __shared__ __attribute__((aligned(16))) float scale[K2];
+    const int tid = threadIdx.x;
+    for (int i = tid; i < K2; i += 256) scale[i] = ascale[i];
+    f2r x[PER];
+    auto load = [&](int64_t t) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int c = tid + 256 * i, r = 2 * (c % (K2 / 2));
+            const int64_t e = t * kTile + c / (K2 / 2);
+            // values outside the sample are read from inside it and replaced when they are staged
+            x[i] = *reinterpret_cast<const f2r *>(A + 2 * (e < n ? e : n - 1) * ld + (r < nreal ? r : 0));
         }
+    };
+    int64_t t = blockIdx.x;
+    if (t < ntiles) load(t);
+    for (; t < ntiles; t += gridDim.x) {
+        __syncthreads();                                // the previous tile's reads are done
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int c = tid + 256 * i, r = 2 * (c % (K2 / 2)), e = c / (K2 / 2);
+            *reinterpret_cast<f2r *>(rows + e * ST + r) = t * kTile + e < n && r < nreal ? x[i] : f2r{0.f, 0.f};
+        }
+        __syncthreads();
+        if (t + gridDim.x < ntiles) load(t + gridDim.x);
         unsigned short *base = out + t * (128 * (int64_t)K2);
-        const float y0 = x0 * ascale[r], y1 = x1 * ascale[r + 1];
-        const _Float16 h0 = (_Float16)y0, h1 = (_Float16)y1;
-        const _Float16 l0 = (_Float16)(y0 - (float)h0), l1 = (_Float16)(y1 - (float)h1);
-        const int pe = 8 * ((e & 15) >> 2) + (e & 3) + 4 * (e >> 4);
-        const __bf16 g0 = (__bf16)x0, g1 = (__bf16)x1;
-        const __bf16 m0 = (__bf16)(x0 - (float)g0), m1 = (__bf16)(x1 - (float)g1);
-        _Float16 *ah = reinterpret_cast<_Float16 *>(base);
-        _Float16 *al = ah + kTile * K2;
-        __bf16 *bh = reinterpret_cast<__bf16 *>(base + 2 * kTile * K2);
-        __bf16 *bl = bh + kTile * K2;
-        ah[e * K2 + r] = h0;
-        ah[e * K2 + r + 1] = h1;
-        al[e * K2 + r] = l0;
-        al[e * K2 + r + 1] = l1;
-        bh[r * kTile + pe] = g0;
-        bh[(r + 1) * kTile + pe] = g1;
-        bl[r * kTile + pe] = m0;
-        bl[(r + 1) * kTile + pe] = m1;
+        for (int u = tid; u < 4 * K2; u += 256) {       // event-major: columns 8 j .. 8 j + 7 of one event
+            const int e = u / (K2 / 8), r = 8 * (u % (K2 / 8));
+            us8 hi, lo;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f4r v = *reinterpret_cast<const f4r *>(rows + e * ST + r + 4 * h) *
+                              *reinterpret_cast<const f4r *>(scale + r + 4 * h);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const _Float16 y = (_Float16)v[i];
+                    hi[4 * h + i] = __builtin_bit_cast(unsigned short, y);
+                    lo[4 * h + i] = __builtin_bit_cast(unsigned short, (_Float16)(v[i] - (float)y));
+                }
+            }
+            *reinterpret_cast<us8 *>(base + e * K2 + r) = hi;
+            *reinterpret_cast<us8 *>(base + kTile * K2 + e * K2 + r) = lo;
+        }
+        for (int u = tid; u < 4 * K2; u += 256) {       // transposed: events 4 q .. and 16 + 4 q .. of one column
+            const int r = u >> 2, q = u & 3;
+            us8 hi, lo;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float v = rows[(16 * (i >> 2) + 4 * q + (i & 3)) * ST + r];
+                const __bf16 y = (__bf16)v;
+                hi[i] = __builtin_bit_cast(unsigned short, y);
+                lo[i] = __builtin_bit_cast(unsigned short, (__bf16)(v - (float)y));
+            }
+            *reinterpret_cast<us8 *>(base + 2 * kTile * K2 + r * kTile + 8 * q) = hi;
+            *reinterpret_cast<us8 *>(base + 3 * kTile * K2 + r * kTile + 8 * q) = lo;
+        }
     }
 }
 
@@ -1060,12 +1097,16 @@ size_t batch_plane_bytes(int64_t n, int k) {
 hipError_t launch_batch_planes(const float *A, int64_t n, int64_t ld, int k, const float *ascale, void *out,
                                hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    const int K2 = 32 * batch_ks(k);
     const int64_t ntiles = (n + kTile - 1) / kTile;
-    const int64_t total = ntiles * kTile * (K2 / 2);
-    const int blocks = (int)std::min<int64_t>((total + 255) / 256, 65536);
-    hipLaunchKernelGGL(batch_planes_kernel, dim3(blocks), dim3(256), 0, stream, A, n, ld, 2 * k, K2, ntiles, ascale,
-                       static_cast<unsigned short *>(out));
+    const dim3 grid((unsigned)std::min<int64_t>(ntiles, 2048)), block(256);
+    unsigned short *o = static_cast<unsigned short *>(out);
+    switch (batch_ks(k)) {
+        case 1: hipLaunchKernelGGL(batch_planes_kernel<1>, grid, block, 0, stream, A, n, ld, 2 * k, ntiles, ascale, o); break;
+        case 2: hipLaunchKernelGGL(batch_planes_kernel<2>, grid, block, 0, stream, A, n, ld, 2 * k, ntiles, ascale, o); break;
+        case 3: hipLaunchKernelGGL(batch_planes_kernel<3>, grid, block, 0, stream, A, n, ld, 2 * k, ntiles, ascale, o); break;
+        case 4: hipLaunchKernelGGL(batch_planes_kernel<4>, grid, block, 0, stream, A, n, ld, 2 * k, ntiles, ascale, o); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
