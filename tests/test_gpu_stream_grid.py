@@ -20,7 +20,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("k,cfg,nb_data,nb_mc", [
     (16, (8, 2, 4), 10, 48), (16, (8, 2, 4), 10, 49), (16, (8, 2, 4), 1, 1), (15, (8, 2, 2), 49, 12),
     (23, (8, 3, 2), 20, 32), (23, (8, 3, 2), 20, 33), (24, (8, 3, 1), 33, 1),
-    (48, (16, 3, 2), 16, 16), (48, (16, 3, 2), 16, 17), (47, (16, 3, 1), 30, 34)])
+    (48, (16, 3, 2), 16, 16), (48, (16, 3, 2), 16, 17), (47, (16, 3, 1), 30, 34),
+    # on either side of the most rows that keep to these blocks (112 KB each)
+    (16, (8, 2, 4), 10, 336), (16, (8, 2, 4), 10, 338), (23, (8, 3, 2), 20, 298), (23, (8, 3, 2), 20, 300),
+    (48, (16, 3, 2), 16, 149), (48, (16, 3, 2), 16, 151)])
 @pytest.mark.parametrize("ragged", [0, 1])
 def test_totals_across_the_limit(k, cfg, nb_data, nb_mc, ragged):
     L, C, U = cfg
