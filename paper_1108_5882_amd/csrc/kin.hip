@@ -45,7 +45,15 @@ namespace {
 constexpr int kKinThreads = 256;
 constexpr int kKinW = 4;            // waves per lane
 constexpr int kKinMaxSpin = 4;
-constexpr int kKinBlocksPerCu = 4;
+// Blocks per CU, by the steps a wave takes when two blocks, as many as fit at once,
+// share a CU.  A block forms its waves' constants and leaves a partial, some 5 us
+// beside the steps; with many steps a second round of blocks evens out the end.  One
+// evaluation at 4, 2 and 1: 4 steps (253 000 events, K = 5) 36.1, 26.6, 25.5 us; 8
+// (500 000, K = 8) 37.7, 28.7, 28.5; 15 (990 000, K = 11) 50.6, 43.7, 45.3; 165
+// (2.7 10^6, K = 18) 131.5, 129.3, 159; 183 (6 10^6, K = 16) 140.3, 141.3, 160.6; 281
+// (4.6 10^6, K = 24) 199.7, 204, 255.
+constexpr int kKinBlocksPerCu = 4;  // at most
+constexpr int kKinManySteps = 168, kKinFewSteps = 6;
 
 struct KinArgs {
     const float2 *mx[2];            // (m, cos theta) per event: data, MC
@@ -456,7 +464,8 @@ pwa_status kin_prepare(pwa_kin *kc, KinArgs &a, int *blocks) {
     const int L = kin_lanes(kc->k);
     const int64_t per_block = (int64_t)(64 / L) * (kKinThreads / 64);
     const int64_t need0 = (a.n[0] + per_block - 1) / per_block, need1 = (a.n[1] + per_block - 1) / per_block;
-    const int64_t budget = kc->max_blocks;
+    const int64_t at_once = 2 * (int64_t)kc->cu_count, steps = (need0 + need1) / at_once;
+    const int64_t budget = steps >= kKinManySteps ? kc->max_blocks : steps >= kKinFewSteps ? at_once : at_once / 2;
     if (need0 + need1 <= budget) {
         a.nb[0] = (int32_t)need0;
         a.nb[1] = (int32_t)need1;
