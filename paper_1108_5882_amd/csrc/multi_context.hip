@@ -32,8 +32,8 @@ struct pwa_multi {
     LbfgsState *d_states = nullptr;
     FitStart *h_start = nullptr;           // mapped host memory, one per fit
     FitResult *h_result = nullptr;
-    int64_t item_bytes = 256 * 1024;       // target bytes of rows per work item
-    int blocks_per_cu = 2;
+    int64_t item_bytes = 0;                // target bytes of rows per work item (default_item_bytes, or tuned)
+    int blocks_per_cu = 1;
     int m = 8;
     double c1 = 1e-4, ftol = 1e-12;
     hipEvent_t ev[2] = {nullptr, nullptr}; // around the steps of a timed call
@@ -74,10 +74,21 @@ struct DevGuard {
     }
 };
 
+// About five items per block, of at least 256 KB: smaller ones pay more starts and
+// partials, larger ones leave blocks idle at the end.  One step (one block per CU):
+// 436 MB of rows 109.0 us in items of 256 KB, 105.8 of 384, 103.1 of 512, 109.3 of 768;
+// 1374 MB 310, 297, 285, 288 and 283 of 1 MB; 214 MB 69 us at 256 and 384 KB, 73 at 128.
+int64_t default_item_bytes(const pwa_multi *m) {
+    int64_t bytes = 0;
+    for (const MultiFit &ft : m->fits) bytes += (ft.n_data + ft.n_mc) * 8 * ft.ld;
+    return std::max<int64_t>(256 << 10, bytes / (5 * m->cu_count));
+}
+
 // Cuts every fit's samples into work items of about item_bytes of rows.
 pwa_status build_items(pwa_multi *m) {
     const int waves = kStreamThreads / 64;
     std::vector<MultiItem> items;
+    if (m->item_bytes == 0) m->item_bytes = default_item_bytes(m);
     for (int f = 0; f < m->nfits; ++f) {
         MultiFit &ft = m->fits[f];
         const int rpt = multi_rows_per_tile(ft.ld);

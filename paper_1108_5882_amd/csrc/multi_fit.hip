@@ -201,14 +201,14 @@ __device__ __forceinline__ void dispatch_item(const MultiItem &it, double *slot,
 }
 
 // A block asks for its next item while it streams the current one, and reads that
-// item's descriptor during the current one's reduction.  Registers of the widest
-// rows allow two blocks per compute unit (a few spilled values are read outside the
-// row loops); without the bound one block fits and its waits are bare.
-// Shares of the rows fixed per block, of equal bytes, took 102 us (fewer items, but
-// the blocks differ in speed), four blocks per compute unit with narrower row
-// shapes 115 us.  24 fits, 475 MB of rows: 92 us (5.2 TB/s); 101 us when a block
-// asked after it had finished, read descriptor, fit and V in turn and stood alone.
-__global__ __launch_bounds__(kMT, 2) void multi_stream_kernel(MultiArgs p) {
+// item's descriptor during the current one's reduction.  One block per compute unit:
+// the widest rows take more than half of its registers, and its four waves keep enough
+// rows in flight (with a bound of 256 registers two blocks fit, and a step of 436 MB
+// took 116 us with two and 110 with one).  Shares of the rows fixed per block, of equal
+// bytes, were slower (the blocks differ in speed).
+// 24 fits, 436 MB of rows: 86 us; 101 us when a block asked after it had finished and
+// read descriptor, fit and V in turn.
+__global__ __launch_bounds__(kMT) void multi_stream_kernel(MultiArgs p) {
     __shared__ int s_next;
     __shared__ double red[kMW * 64 * kRedSlot];
     // descriptors through the scalar cache, apart from the rows in flight
