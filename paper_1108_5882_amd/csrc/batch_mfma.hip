@@ -932,19 +932,21 @@ __global__ __launch_bounds__(kCombineThreads) void nll_batch_combine_kernel(Batc
 // What lies between two passes of a fit, in one launch: the vector's sums, its
 // L-BFGS update and the weights of its next trial point, which the update leaves in
 // the state (p.V points into it).  Bound by latency; the state is loaded before the
-// partials' sums.  32 vectors at K = 8, 24000 rows: 13.8 us; 23 us in four launches
-// (combine 7.3, update 6.2, scales 4.5, fragments 4.7), one vector's |V|^2
-// formed by every block of the pass (12.6 us, now 8.7).
-template <int KS, int CT>
+// partials' sums, and the two parametrisations are kernels of their own: the code runs
+// once per launch, so its size counts (86 KB of it with both: 15.0 us, 26 KB: 12.5).
+// 32 vectors at K = 8, 20000 rows: 12.5 us; 23 us in four launches (combine 7.3,
+// update 6.2, scales 4.5, fragments 4.7), one vector's |V|^2 formed by every block of
+// the pass (12.6 us, now 8.5).
+template <int KS, int CT, bool POLAR>
 __global__ __launch_bounds__(kCombineThreads) void batch_step_kernel(BatchArgs p, LbfgsState *states, double c1,
-                                                                     double ftol, int polar, double rmin) {
+                                                                     double ftol, double rmin) {
     __shared__ CombineSmem sm;
     const int v = blockIdx.x, n = 2 * p.k;
     const bool first = threadIdx.x < 64;
     LbRegs r;
     float sc[kLbfgsPer];
     if (first) {
-        lbfgs_load(r, states + v, n, polar != 0);
+        lbfgs_load(r, states + v, n, POLAR);
         lane_scales(p, sc);
     }
     double nll;
@@ -952,7 +954,7 @@ __global__ __launch_bounds__(kCombineThreads) void batch_step_kernel(BatchArgs p
     LbVec grad;
     combine_vector(p, v, sm, nll, flags, grad);
     if (!first) return;
-    const LbVec next = lbfgs_advance(states + v, r, n, nll, grad, c1, ftol, polar != 0, rmin, sm.pl);
+    const LbVec next = lbfgs_advance(states + v, r, n, nll, grad, c1, ftol, POLAR, rmin, sm.pl);
     vector_weights<KS, CT>(p, v, next, sc, sm.ps);
 }
 
@@ -1125,9 +1127,15 @@ hipError_t launch_batch_combine(const BatchArgs &args, hipStream_t stream) {
 hipError_t launch_batch_step(const BatchArgs &args, LbfgsState *states, double c1, double ftol, bool polar, double rmin,
                              hipStream_t stream) {
     const dim3 grid(args.nv), block(kCombineThreads);
-#define PWA_BATCH_STEP(KS_, CT_)                                                                                     \
-    hipLaunchKernelGGL((batch_step_kernel<KS_, CT_>), grid, block, 0, stream, args, states, c1, ftol, polar ? 1 : 0, \
-                       rmin)
+#define PWA_BATCH_STEP(KS_, CT_)                                                                                      \
+    do {                                                                                                              \
+        if (polar)                                                                                                    \
+            hipLaunchKernelGGL((batch_step_kernel<KS_, CT_, true>), grid, block, 0, stream, args, states, c1, ftol,   \
+                               rmin);                                                                                 \
+        else                                                                                                          \
+            hipLaunchKernelGGL((batch_step_kernel<KS_, CT_, false>), grid, block, 0, stream, args, states, c1, ftol,  \
+                               rmin);                                                                                 \
+    } while (0)
     switch (batch_ks(args.k)) {
         case 1: PWA_BATCH_STEP(1, 4); break;
         case 2: PWA_BATCH_STEP(2, 4); break;

@@ -71,7 +71,8 @@ __device__ __forceinline__ LbVec lb_axpy(const LbVec &a, double s, const LbVec &
 }
 // Products in LDS, added in index order by every lane (a wave's LDS operations
 // complete in order; the fences only keep the compiler's order).  p: 64 kLbfgsPer
-// doubles of LDS of this wave.
+// doubles of LDS of this wave.  The loops stay rolled beyond 16 terms: an update runs
+// some 20 of these once each, and its time follows the size of the code it fetches.
 __device__ __forceinline__ double lb_dot(const LbVec &a, const LbVec &b, int n, double *p) {
     const int lane = threadIdx.x & 63;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -80,6 +81,7 @@ __device__ __forceinline__ double lb_dot(const LbVec &a, const LbVec &b, int n, 
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     double s = 0.0;
     int i = 0;
+#pragma clang loop unroll(disable)
     for (; i + 16 <= n; i += 16) {
         double v[16];
 #pragma unroll
@@ -87,6 +89,7 @@ __device__ __forceinline__ double lb_dot(const LbVec &a, const LbVec &b, int n, 
 #pragma unroll
         for (int j = 0; j < 16; ++j) s += v[j];
     }
+#pragma clang loop unroll(disable)
     for (; i < n; i += 2) {                               // n is even
         s += p[i];
         s += p[i + 1];
