@@ -620,7 +620,7 @@ pwa_status pwa_kin_nll_grad(pwa_kin *kc, const double *V, const double *res, dou
     // the kernel writes the result to mapped host memory, then the sequence number
     const volatile unsigned long long *done = kc->done_host;
     for (unsigned spin = 1; *done != a.seq; ++spin) {
-        if ((spin & 4095u) == 0) {
+        if ((spin & 65535u) == 0) {
             const hipError_t q = hipStreamQuery(kc->stream);
             if (q == hipSuccess) {
                 if (*done == a.seq) break;
