@@ -209,8 +209,22 @@ pwa_status grow(pwa_ctx *ctx, void **buf, size_t *cap, size_t bytes, const char 
     return PWA_OK;
 }
 
+// PWA_E_HIP while the context's stream is capturing.  Work recorded into a graph has
+// not run when the call returns: what a context builds once and later calls rely on
+// must not be built there, and a call that waits must not leave part of itself in the
+// graph.
+pwa_status refuse_capture(pwa_ctx *ctx, const char *what) {
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    PWA_HIP(ctx, hipStreamIsCapturing(ctx->stream, &capturing), "hipStreamIsCapturing");
+    if (capturing != hipStreamCaptureStatusNone)
+        return fail(ctx, PWA_E_HIP, "%s: the context's stream is capturing", what);
+    return PWA_OK;
+}
+
 pwa_status ensure_gram(pwa_ctx *ctx) {
     if (ctx->gram_valid) return PWA_OK;
+    pwa_status st = refuse_capture(ctx, "MC matrix");
+    if (st != PWA_OK) return st;
     const Sample &mc = ctx->s[1];
     if (!ctx->gram) PWA_HIP(ctx, hipMalloc(&ctx->gram, sizeof(double) * 2 * PWA_MAX_K * PWA_MAX_K),
                             "hipMalloc(gram)");
@@ -220,8 +234,8 @@ pwa_status ensure_gram(pwa_ctx *ctx) {
     } else {
         const int blocks = (int)std::min<int64_t>((int64_t)ctx->cu_count * 2, (mc.n + 63) / 64);
         // everything that reads the matrix is ordered after its build on the context's stream
-        pwa_status st = grow(ctx, &ctx->g_buf, &ctx->g_cap, sizeof(double) * gram_partial_doubles(ctx->k, blocks),
-                             "hipMalloc(gram partials)");
+        st = grow(ctx, &ctx->g_buf, &ctx->g_cap, sizeof(double) * gram_partial_doubles(ctx->k, blocks),
+                  "hipMalloc(gram partials)");
         if (st != PWA_OK) return st;
         PWA_HIP(ctx, launch_gram(ctx->prec, mc.A, mc.w, mc.n, ctx->ld, ctx->k, mc.n_gen,
                                  static_cast<double *>(ctx->g_buf), blocks, ctx->gram, ctx->stream),
@@ -565,7 +579,8 @@ pwa_status batch_mfma(pwa_ctx *ctx, int32_t nv, const double *V, double *nll, do
     DeviceGuard dg(ctx->device);
     const int k = ctx->k;
     const size_t out_doubles = (size_t)nv * (2 * k + 2);
-    pwa_status st;
+    pwa_status st = refuse_capture(ctx, "batched NLL");
+    if (st != PWA_OK) return st;
     if ((st = grow(ctx, &ctx->b_V, &ctx->b_cap[3], sizeof(double) * 2 * k * (size_t)nv, "hipMalloc(V)")) ||
         (st = grow(ctx, &ctx->b_out, &ctx->b_cap[5], sizeof(double) * out_doubles, "hipMalloc(out)")))
         return st;
@@ -661,13 +676,10 @@ pwa_status pwa_batch_fit(pwa_ctx *ctx, int32_t nv, const double *V0, int32_t ite
     DeviceGuard dg(ctx->device);
     BatchArgs a;
     int gpad = 0;
-    pwa_status st = batch_setup(ctx, nv, a, &gpad);
+    pwa_status st = refuse_capture(ctx, "batched fit");
     if (st != PWA_OK) return st;
+    if ((st = batch_setup(ctx, nv, a, &gpad)) != PWA_OK) return st;
     if (a.n[0] > 0 && (st = refine_setup(ctx, nv, a, true)) != PWA_OK) return st;
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    PWA_HIP(ctx, hipStreamIsCapturing(ctx->stream, &capturing), "hipStreamIsCapturing");
-    if (capturing != hipStreamCaptureStatusNone)
-        return fail(ctx, PWA_E_HIP, "batched fit: the context's stream is capturing");
     if ((st = grow(ctx, &ctx->f_states, &ctx->f_cap, sizeof(LbfgsState) * (size_t)nv, "hipMalloc(states)")) != PWA_OK)
         return st;
     const size_t host_bytes = (sizeof(FitStart) + sizeof(FitResult)) * (size_t)nv;
