@@ -31,6 +31,7 @@
 #include "internal.hpp"
 #include "lane_ops.hpp"
 #include "lbfgs_device.hpp"
+#include "row_norm.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -653,23 +654,19 @@ __global__ __launch_bounds__(256) void batch_planes_kernel(const float *A, int64
 }
 
 // |A_i|^2 of each row (FP64 sums of the FP32 values, stored as FP32): 8 lanes per
-// row, each reading 16-byte chunks (two complex values), summed over the 8 lanes.
-// Only the first k complex values count (a borrowed sample's padding is not read
-// as data).  Rows are 16-byte aligned (ld even).
+// row, summed over the 8 lanes.  Only the first k complex values count (a borrowed
+// sample's padding is not read as data).
 __global__ void rownorm_kernel(const float *A, int64_t n, int64_t ld, int k, float *out) {
+    typedef float f2r __attribute__((ext_vector_type(2)));
     typedef float f4r __attribute__((ext_vector_type(4)));
     const int sub = threadIdx.x & 7;
-    const int nch = (k + 1) / 2;
     const int64_t groups = (int64_t)gridDim.x * blockDim.x / 8;
     // the 8 lanes of a row share r, so they leave the loop together
     for (int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 8; r < n; r += groups) {
-        const f4r *x = reinterpret_cast<const f4r *>(A + 2 * r * ld);
-        double s = 0.0;
-        for (int c = sub; c < nch; c += 8) {
-            const f4r v = x[c];
-            s += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
-            if (2 * c + 1 < k) s += (double)v.z * (double)v.z + (double)v.w * (double)v.w;
-        }
+        const float *row = A + 2 * r * ld;
+        double s = row_norm_share(
+            k, ld % 2 == 0, sub, [=](int c) { return reinterpret_cast<const f4r *>(row)[c]; },
+            [=](int a) { return reinterpret_cast<const f2r *>(row)[a]; });
         s += __shfl_xor(s, 1);
         s += __shfl_xor(s, 2);
         s += __shfl_xor(s, 4);
