@@ -897,10 +897,15 @@ pwa_status pwa_set_amplitudes(pwa_ctx *ctx, pwa_set which, const void *A, int64_
     Sample &s = ctx->s[which];
     if (s.owned && (s.A || s.w) && where != PWA_BORROW && n > 0) {
         // the memory is kept for the new sample: everything enqueued on the device
-        // comes first, as a free would make it
+        // comes first, as a free would make it.  hipDeviceSynchronize would fail, and
+        // end the capture, while any stream of the process is capturing; an allocation
+        // and a free, which waits for the device, are refused only where those of a new
+        // sample would be
         s.set = false;
         s.n = 0;
-        PWA_HIP(ctx, hipDeviceSynchronize(), "hipDeviceSynchronize");
+        void *token = nullptr;
+        PWA_HIP(ctx, hipMalloc(&token, 256), "hipMalloc(amplitudes)");
+        PWA_HIP(ctx, hipFree(token), "hipFree(amplitudes)");
     } else {
         free_sample(s);
     }
