@@ -138,8 +138,8 @@ int grid_of(const pwa_multi *m) {
     return std::max(1, std::min(m->n_items, m->cu_count * m->blocks_per_cu));
 }
 
-// Writes every fit's start vector into its L-BFGS state (phase 0).  The stream is idle
-// on entry: nothing reads the records of an earlier start.
+// Writes every fit's start vector into its L-BFGS state (phase 0) and waits for it: the
+// records are free again, and an error is this call's, when it returns.
 pwa_status reset_states(pwa_multi *m, const double *V0) {
     size_t off = 0;
     for (int f = 0; f < m->nfits; ++f) {
@@ -149,6 +149,7 @@ pwa_status reset_states(pwa_multi *m, const double *V0) {
         off += n;
     }
     M_HIP(m, launch_fit_start(m->d_states, m->h_start, m->nfits, m->stream), "start launch");
+    M_HIP(m, hipStreamSynchronize(m->stream), "hipStreamSynchronize");
     return PWA_OK;
 }
 
