@@ -248,20 +248,101 @@ __global__ __launch_bounds__(kMT) void multi_stream_kernel(MultiArgs p) {
 // One block per fit: adds the fit's item partials and forms NLL and gradient
 // (Eq. 2 form).  Slice s of a column adds items i0 + s, i0 + s + kSlices, ...; the
 // slices are then added in slice order, so the result does not depend on which
-// block evaluated which item.  A thread's sums (up to kSums of both samples) go
-// through their items side by side.
+// block evaluated which item.  A wave takes two slices, its lanes the columns (two
+// each in fits of more than 31 waves), so that a slice's items are counted per wave
+// and whole partials are read; the first items of both samples are read together.
 //
 // With STEP the first wave then advances the fit's L-BFGS state, loaded ahead of the
-// partials; otherwise the result goes to out[fit][2k + 2].  Bound by latency: 24
-// fits of up to 48 waves 16.5 us; the sums (7.6) and the
-// update (9.3) were two launches, some 4 us apart.
+// partials; otherwise the result goes to out[fit][2k + 2].  Bound by latency with few
+// items per fit, by what one CU reads with many.  64 fits, 11.8 GB of rows, sums alone:
+// 328 us in items of 64 KB, 94 of 256 KB, 28 of 1 MB, 9.7 of 4 MB; 428, 120, 34 and
+// 12.2 us with one sum per thread and a load of its own for each (1024 threads), 487,
+// 138, 39 and 12.7 us when a thread read an item for all of its sums in every round,
+// whether they had one or not.  With the update 22.7 us (4 MB).
 constexpr int kCombineThreads = 512;
 constexpr int kSlices = 16;
+constexpr int kWaveSlices = kSlices / (kCombineThreads / 64);
+constexpr int kAhead = 4;                              // items of a slice in flight
+
+// Sums of a wave's slices of one sample: items first + sl + 16 t of n, t in order.
+// NC: columns per lane; lanes past the last column read it again.
+template <int NC>
+struct SliceSums {
+    typedef const double __attribute__((address_space(1))) *gptr;
+    gptr src[NC];
+    int last;                                          // of the sample's items, from src on
+    int count[kWaveSlices];                            // items of each slice
+    double s[kWaveSlices][NC], x[kAhead][kWaveSlices][NC];
+
+    __device__ __forceinline__ SliceSums(const double *partials, int first, int n, int sl, int ps) {
+        const int lane = threadIdx.x & 63;
+        // a sample without items reads the first partial
+        gptr base = (gptr)partials + (n > 0 ? (int64_t)(first + (sl < n ? sl : 0)) * kMultiSlot : 0);
+        last = max(n - 1 - sl, 0);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) src[c] = base + min(lane + 64 * c, ps - 1);
+#pragma unroll
+        for (int j = 0; j < kWaveSlices; ++j) {
+            count[j] = n > sl + j ? (n - sl - j + kSlices - 1) / kSlices : 0;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) s[j][c] = 0.0;
+        }
+    }
+    // items t .. t + kAhead - 1; in the place of those past the slice's last, the
+    // sample's last one (no branch around the loads, at whose join they would be waited for)
+    __device__ __forceinline__ void load(int t) {
+#pragma unroll
+        for (int h = 0; h < kAhead; ++h)
+#pragma unroll
+            for (int j = 0; j < kWaveSlices; ++j) {
+                const int64_t i = min((t + h) * kSlices + j, last);
+#pragma unroll
+                for (int c = 0; c < NC; ++c) x[h][j][c] = src[c][i * kMultiSlot];
+            }
+    }
+    __device__ __forceinline__ void add(int t) {
+#pragma unroll
+        for (int h = 0; h < kAhead; ++h)
+#pragma unroll
+            for (int j = 0; j < kWaveSlices; ++j)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) s[j][c] += t + h < count[j] ? x[h][j][c] : 0.0;     // no sum is -0
+    }
+};
+
+template <int NC>
+__device__ __forceinline__ void slice_sums(const MultiArgs &p, const MultiFit &fit, int ps,
+                                           double (*part)[2][1 + 2 * kMultiMaxLd]) {
+    const int lane = threadIdx.x & 63, sl = kWaveSlices * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    SliceSums<NC> d(p.partials, fit.item_data0, fit.item_data1 - fit.item_data0, sl, ps);
+    SliceSums<NC> m(p.partials, fit.item_mc0, fit.item_mc1 - fit.item_mc0, sl, ps);
+    if (d.count[0] + m.count[0] > 0) {
+        d.load(0);
+        m.load(0);
+        d.add(0);
+        m.add(0);
+    }
+    for (int t = kAhead; t < d.count[0]; t += kAhead) {
+        d.load(t);
+        d.add(t);
+    }
+    for (int t = kAhead; t < m.count[0]; t += kAhead) {
+        m.load(t);
+        m.add(t);
+    }
+#pragma unroll
+    for (int j = 0; j < kWaveSlices; ++j)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            if (lane + 64 * c < ps) {
+                part[sl + j][0][lane + 64 * c] = d.s[j][c];
+                part[sl + j][1][lane + 64 * c] = m.s[j][c];
+            }
+}
 
 template <bool STEP>
 __global__ __launch_bounds__(kCombineThreads) void multi_combine_kernel(MultiArgs p, LbfgsState *states, double c1,
                                                                         double ftol) {
-    constexpr int kSums = (kSlices * 2 * (1 + 2 * kMultiMaxLd) + kCombineThreads - 1) / kCombineThreads;
     __shared__ double part[kSlices][2][1 + 2 * kMultiMaxLd];
     __shared__ double tot[2][1 + 2 * kMultiMaxLd];
     __shared__ double prod[64 * kLbfgsPer];
@@ -270,37 +351,8 @@ __global__ __launch_bounds__(kCombineThreads) void multi_combine_kernel(MultiArg
     const int k = fit.k, ps = 1 + 2 * (int)fit.ld;
     LbRegs r;
     if (STEP && tid < 64) lbfgs_load(r, states + f, 2 * k, false);
-    const int n0 = fit.item_data1 - fit.item_data0, n1 = fit.item_mc1 - fit.item_mc0;
-    double s[kSums];
-    const double *src[kSums];
-    int left[kSums];                                   // items of the sum not yet added
-#pragma unroll
-    for (int u = 0; u < kSums; ++u) {
-        const int idx = tid + u * kCombineThreads, sl = idx / (2 * ps), rem = idx - sl * 2 * ps;
-        const int sg = rem >= ps;
-        const int n = sl >= kSlices ? 0 : (sg ? n1 : n0) - sl;
-        s[u] = 0.0;
-        left[u] = n > 0 ? (n + kSlices - 1) / kSlices : 0;
-        // a sum without items reads the first partial
-        src[u] = p.partials +
-                 (left[u] ? (int64_t)((sg ? fit.item_mc0 : fit.item_data0) + sl) * kMultiSlot + rem - sg * ps : 0);
-    }
-    const int trips = (max(n0, n1) + kSlices - 1) / kSlices;
-    for (int i = 0; i < trips; ++i) {
-        double x[kSums];
-#pragma unroll
-        for (int u = 0; u < kSums; ++u) x[u] = *src[u];
-#pragma unroll
-        for (int u = 0; u < kSums; ++u) {
-            if (left[u] > 0) s[u] += x[u];
-            if (--left[u] > 0) src[u] += kSlices * kMultiSlot;     // past its last item a sum reads that one again
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < kSums; ++u) {
-        const int idx = tid + u * kCombineThreads, sl = idx / (2 * ps), rem = idx - sl * 2 * ps;
-        if (sl < kSlices) part[sl][rem >= ps][rem >= ps ? rem - ps : rem] = s[u];
-    }
+    if (ps <= 64) slice_sums<1>(p, fit, ps, part);
+    else slice_sums<2>(p, fit, ps, part);
     __syncthreads();
     for (int idx = tid; idx < 2 * ps; idx += kCombineThreads) {
         const int sg = idx >= ps, cc = idx - sg * ps;
