@@ -40,8 +40,16 @@
  * abort, print or throw; pwa_last_error() describes the last failure.
  *
  * Concurrency: a context is not thread-safe.  All its device work is ordered
- * on its stream.  The synchronous calls wait on that stream; the _async calls
- * neither wait nor allocate, so they can be captured into a HIP graph.
+ * on its stream.  The synchronous calls wait on that stream, and return PWA_E_HIP
+ * while it is capturing; the _async calls neither wait nor allocate, so they can
+ * be captured into a HIP graph.
+ *
+ * Memory: beside its samples a context keeps the workspaces of its calls until it
+ * is destroyed, each as large as its largest use: block partials of the MC matrix
+ * (33 MB at most), of the Hessian and of the batched pass, the batched pass's
+ * operand planes, row norms, flags and weights, and the L-BFGS states of fits of
+ * up to 4096 starts (117 MB of device and 10 MB of pinned memory; those of larger
+ * fits are freed when the call returns).
  */
 #ifndef PWA_H
 #define PWA_H
@@ -106,7 +114,9 @@ pwa_status pwa_destroy(pwa_ctx *ctx);
  *   n_gen  MC only: number of generated events N_gen of Eq. 3's 1/N_gen;
  *          <= 0 means n.  Ignored for data.
  * Replacing a sample whose k differs from the other sample's drops the other
- * sample.  Errors: PWA_E_INVAL, PWA_E_NOMEM, PWA_E_HIP, PWA_E_UNSUPPORTED. */
+ * sample.  A copied sample that replaces a copied one takes over its memory when
+ * it fits there and leaves at most half of it idle; otherwise, and when it is
+ * empty or borrowed, that memory is freed.  Errors: PWA_E_INVAL, PWA_E_NOMEM, PWA_E_HIP, PWA_E_UNSUPPORTED. */
 pwa_status pwa_set_amplitudes(pwa_ctx *ctx, pwa_set which, const void *A, int64_t n,
                               int32_t k, int64_t ld, pwa_where where, const void *w,
                               double n_gen);
