@@ -495,7 +495,6 @@ pwa_status batch_setup(pwa_ctx *ctx, int32_t nv, BatchArgs &a, int *gpad, bool a
         }
         a.planes[sg] = ctx->b_planes[sg];
     }
-    a.ngroups_pad = *gpad;
     // c^2 of the flag test: sqrt(k) / N_D, at most 1/64.  An unflagged event's
     // error in conj(A) z / I is at most about eps sqrt(k) / c^2 (in units of
     // 1/|V|) while the gradient scale grows with N_D, so c^2 proportional to

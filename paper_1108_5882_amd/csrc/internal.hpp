@@ -125,7 +125,6 @@ struct BatchArgs {
     const float *rnorm;        // |A_i|^2 per data row
     unsigned long long *flags; // batch_flag_words() lane masks
     float cthr2;               // c^2 of the flag test |z| < c |V| |A_i|
-    int32_t ngroups_pad;       // vector groups rounded up to whole blocks
 };
 
 constexpr int kTilesPerBlock = 128;  // most tiles a block of the batched pass takes
@@ -211,6 +210,8 @@ struct LbfgsState {
     double f, alpha, gtd;
     int32_t head, count, phase, iter, status, nbacktrack;
 };
+static_assert(sizeof(LbfgsState) % 16 == 0 && offsetof(LbfgsState, xt) % 16 == 0 && offsetof(LbfgsState, vt) % 16 == 0,
+              "evaluations read trial points of an array of states in 16-byte pairs");
 
 // Records of a fit in mapped host memory: its start (the trial point, and in polar
 // form the V it stands for) and its result.
