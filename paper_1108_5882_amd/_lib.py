@@ -705,7 +705,7 @@ class MultiFit:
         self._check(self.lib.pwa_multi_reset(self.h, _ptr(v)))
 
     def step(self, steps: int = 1) -> float:
-        """Replay `steps` minimiser iterations; returns the average ms per iteration."""
+        """Run `steps` minimiser iterations; returns the average ms per iteration."""
         ms = ctypes.c_double()
         self._check(self.lib.pwa_multi_step(self.h, int(steps), ctypes.byref(ms)))
         return ms.value

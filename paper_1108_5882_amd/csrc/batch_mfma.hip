@@ -455,10 +455,14 @@ __global__ __launch_bounds__(kThreads) void nll_batch_kernel(BatchArgs p) {
 // one wave, in that fixed order.
 //
 // Bound: latency (flag words, then rows; few events are flagged).  256 vectors at
-// K = 32, 2 10^6 data rows: 128 us; 32 vectors at K = 8 on 4000 rows (one group):
-// 5.6 us on average over a fit.  201 and 13.3 us when one wave per group took one
-// event after the other, each with a row load, twelve lane shuffles through LDS
-// and an update of the partial in memory.
+// K = 32, 2 10^6 data rows, of the cases in perf/cases.py (115,709 events flagged,
+// 33,758 of them by one vector): 132 us, and 207 us when one wave per group took one
+// event after the other, each with a row load, twelve lane shuffles through LDS and an
+// update of the partial in memory.  On the sample of the same size in synth (80,844
+// flagged, at most 5,672 by one vector) there is less to put side by side: 106 us, 103
+// one after the other.  32 vectors at K = 8 on 4000 rows (one group): 5.6 us on average
+// over a fit, 13.3 one after the other.  Not kept: the next 512 words asked for during
+// the present ones (155 and 140 us: they queue ahead of the rows).
 constexpr int kRefineLoads = 8;                     // flag words per lane and chunk
 constexpr int kRefineRounds = 4;                    // rounds of rows in flight
 constexpr unsigned long long kEveryRow16 = 0x0001000100010001ull;

@@ -51,7 +51,8 @@ constexpr int kKinMaxSpin = 4;
 // evaluation at 4, 2 and 1: 4 steps (253 000 events, K = 5) 36.1, 26.6, 25.5 us; 8
 // (500 000, K = 8) 37.7, 28.7, 28.5; 15 (990 000, K = 11) 50.6, 43.7, 45.3; 165
 // (2.7 10^6, K = 18) 131.5, 129.3, 159; 183 (6 10^6, K = 16) 140.3, 141.3, 160.6; 281
-// (4.6 10^6, K = 24) 199.7, 204, 255.
+// (4.6 10^6, K = 24) 199.7, 204, 255.  Four and two meet between 165 and 183 steps, to
+// 2% on either side: the line lies there.
 constexpr int kKinBlocksPerCu = 4;  // at most
 constexpr int kKinManySteps = 168, kKinFewSteps = 6;
 

@@ -1,6 +1,6 @@
 // Device L-BFGS for many independent fits (one wave per fit), advanced once
 // per evaluation so that the whole iteration (evaluate every fit's trial
-// point, then update every fit) can be captured in a HIP graph.
+// point, then update every fit) stays on the device.
 //
 // Each fit minimises its NLL over the real vector x = (Re V_0, Im V_0, ...)
 // (minimisers work on real parameters, Berger Section 4).  State machine per

@@ -10,8 +10,10 @@
 // and used in FP16 by the matrix cores; every GEMM rounds both operands to
 // FP16 when they are staged and accumulates in FP32 (v_mfma_f32_16x16x32_f16).
 // Loss: mean squared error.  Optimiser: Adam (0.9, 0.999, 1e-8) on the FP32
-// master weights.  The kernels of a training step are captured in HIP graphs
-// (one step, and groups of 16 steps) and replayed.
+// master weights.  These are the general kernels: their training steps are captured
+// in HIP graphs (one step, and groups of 16 steps) and replayed.  At hidden width
+// 256 training takes the two launches of mlp_fused.hip, and inference with up to 64
+// inputs the one of mlp_predict.hip.
 #include "internal.hpp"
 #include "lane_ops.hpp"
 

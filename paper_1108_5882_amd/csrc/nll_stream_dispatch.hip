@@ -75,6 +75,11 @@ StreamCfg stream_default_cfg(pwa_prec prec, int ld) {
     // and a ragged end.  256 against 1024 blocks, one evaluation: 20 MB of rows 19.7 /
     // 25.4 us at K = 16, 19.3 / 22.3 at 23; 60 MB 25.5 / 29.6 and 25.5 / 27.2; 180 MB
     // 42.4 / 49.8; 720 MB 129.9 / 132.2 (numbers between multiples of the CUs are worse).
+    // At other widths and in FP64, these rules and those of stream_grid together against
+    // 1024 blocks: K = 48 FP32, 20,000 rows 17.6 / 21.0 us, 300,000 33.4 / 38.6, 1.2 10^6
+    // 88.6 / 94.1; K = 64 20.4 / 24.3, 40.6 / 48.2, 112 / 120; FP64 with half the rows
+    // K = 2 14.3 / 16.8, 15.9 / 18.7, 17.6 / 22.3, K = 64 19.8 / 23.7, 42.6 / 47.9,
+    // 116 / 122.
     const Table &t = table(prec);
     const int eb = prec == PWA_F32 ? 8 : 16;
     StreamCfg best{0, 0, 0, 1};
