@@ -233,7 +233,9 @@ pwa_status ensure_gram(pwa_ctx *ctx) {
                 "hipMemsetAsync(gram)");
     } else {
         const int blocks = (int)std::min<int64_t>((int64_t)ctx->cu_count * 2, (mc.n + 63) / 64);
-        // everything that reads the matrix is ordered after its build on the context's stream
+        // everything that reads the matrix is ordered after its build on the context's stream.
+        // The build reads a sample, which may be the caller's own array: a synchronous call
+        // starts it after all else that can fail, or waits before it returns with an error
         st = grow(ctx, &ctx->g_buf, &ctx->g_cap, sizeof(double) * gram_partial_doubles(ctx->k, blocks),
                   "hipMalloc(gram partials)");
         if (st != PWA_OK) return st;
@@ -245,20 +247,25 @@ pwa_status ensure_gram(pwa_ctx *ctx) {
     return PWA_OK;
 }
 
-// Validates state and fills the launch arguments; *blocks = 0 means nothing to launch.
-pwa_status prepare(pwa_ctx *ctx, StreamArgs &a, int *blocks) {
+// Validates state and V (host, or null when the kernel reads V on the device) and fills
+// the launch arguments; *blocks = 0 means nothing to launch.
+pwa_status prepare(pwa_ctx *ctx, const double *V, StreamArgs &a, int *blocks) {
     if (!ctx->s[0].set) return fail(ctx, PWA_E_STATE, "data sample not set");
     const int64_t nd = ctx->s[0].n;
     const bool need_mc = ctx->extended || nd > 0;
     if (need_mc && !ctx->s[1].set) return fail(ctx, PWA_E_STATE, "MC sample not set");
     if (need_mc && ctx->s[1].n == 0 && nd > 0)
         return fail(ctx, PWA_E_STATE, "MC sample is empty: no normalisation");
+    std::memset(&a, 0, sizeof a);
+    for (int i = 0; V && i < 2 * ctx->k; ++i) {
+        if (!std::isfinite(V[i])) return fail(ctx, PWA_E_INVAL, "V[%d] is not finite", i);
+        a.v_arg[i] = V[i];
+    }
     const bool gram = ctx->mode == PWA_MC_GRAM;
     if (gram && need_mc) {
         pwa_status st = ensure_gram(ctx);
         if (st != PWA_OK) return st;
     }
-    std::memset(&a, 0, sizeof a);
     a.A[0] = ctx->s[0].A;
     a.A[1] = ctx->s[1].A;
     a.w = ctx->s[1].w;
@@ -343,13 +350,9 @@ pwa_status eval_sync(pwa_ctx *ctx, const double *V, double *nll, double *grad) {
     DeviceGuard dg(ctx->device);
     StreamArgs a;
     int blocks = 0;
-    pwa_status st = prepare(ctx, a, &blocks);
+    pwa_status st = prepare(ctx, V, a, &blocks);
     if (st != PWA_OK) return st;
     const int k = ctx->k;
-    for (int i = 0; i < 2 * k; ++i) {
-        if (!std::isfinite(V[i])) return fail(ctx, PWA_E_INVAL, "V[%d] is not finite", i);
-        a.v_arg[i] = V[i];
-    }
     double *res = ctx->out_host;
     if (blocks == 0 && !a.gram) {
         trivial_result(ctx, res);
@@ -586,8 +589,10 @@ pwa_status batch_mfma(pwa_ctx *ctx, int32_t nv, const double *V, double *nll, do
     PWA_HIP(ctx, hipMemcpyAsync(ctx->b_V, V, sizeof(double) * 2 * k * (size_t)nv, hipMemcpyHostToDevice,
                                 ctx->stream), "hipMemcpyAsync(V)");
     if ((st = batch_launch(ctx, nv, static_cast<const double *>(ctx->b_V), static_cast<double *>(ctx->b_out),
-                           refine, true)) != PWA_OK)
+                           refine, true)) != PWA_OK) {
+        (void)hipStreamSynchronize(ctx->stream);     // matrix, planes or row norms may be under way
         return st;
+    }
     std::vector<double> out(out_doubles);
     PWA_HIP(ctx, hipMemcpyAsync(out.data(), ctx->b_out, sizeof(double) * out_doubles, hipMemcpyDeviceToHost,
                                 ctx->stream), "hipMemcpyAsync(result)");
@@ -694,18 +699,24 @@ pwa_status pwa_batch_fit(pwa_ctx *ctx, int32_t nv, const double *V0, int32_t ite
             ctx->f_cap = ctx->f_host_cap = 0;
         }
     } give_back{ctx, nv};
-    if ((st = batch_setup(ctx, nv, a, &gpad)) != PWA_OK) return st;
-    if (a.n[0] > 0 && (st = refine_setup(ctx, nv, a, true)) != PWA_OK) return st;
-    if ((st = grow(ctx, &ctx->f_states, &ctx->f_cap, sizeof(LbfgsState) * (size_t)nv, "hipMalloc(states)")) != PWA_OK)
-        return st;
-    const size_t host_bytes = (sizeof(FitStart) + sizeof(FitResult)) * (size_t)nv;
-    if (ctx->f_host_cap < host_bytes) {
+    auto workspace = [&]() -> pwa_status {
+        if ((st = batch_setup(ctx, nv, a, &gpad)) != PWA_OK) return st;
+        if (a.n[0] > 0 && (st = refine_setup(ctx, nv, a, true)) != PWA_OK) return st;
+        if ((st = grow(ctx, &ctx->f_states, &ctx->f_cap, sizeof(LbfgsState) * (size_t)nv, "hipMalloc(states)")) != PWA_OK)
+            return st;
+        const size_t host_bytes = (sizeof(FitStart) + sizeof(FitResult)) * (size_t)nv;
+        if (ctx->f_host_cap >= host_bytes) return PWA_OK;
         if (ctx->f_host) (void)hipHostFree(ctx->f_host);
         ctx->f_host = nullptr;
         ctx->f_host_cap = 0;
         PWA_HIP(ctx, hipHostMalloc(&ctx->f_host, host_bytes, hipHostMallocMapped | hipHostMallocCoherent),
                 "hipHostMalloc(fits)");
         ctx->f_host_cap = host_bytes;
+        return PWA_OK;
+    };
+    if ((st = workspace()) != PWA_OK) {
+        (void)hipStreamSynchronize(ctx->stream);     // matrix, planes or row norms may be under way
+        return st;
     }
     // L-BFGS states: the matrix-core pass reads each vector's trial point in place
     // (xt, or in polar form the V it stands for, vt)
@@ -993,7 +1004,7 @@ pwa_status pwa_nll_grad_async(pwa_ctx *ctx, const double *V_dev, double *out_dev
     DeviceGuard dg(ctx->device);
     StreamArgs a;
     int blocks = 0;
-    pwa_status st = prepare(ctx, a, &blocks);
+    pwa_status st = prepare(ctx, nullptr, a, &blocks);
     if (st != PWA_OK) return st;
     a.v_dev = V_dev;
     a.out = out_dev;
@@ -1069,7 +1080,7 @@ pwa_status pwa_hessian(pwa_ctx *ctx, const double *V, double *H) {
     if (need_mc && !ctx->s[1].set) return fail(ctx, PWA_E_STATE, "MC sample not set");
     if (need_mc && ctx->s[1].n == 0 && nd > 0) return fail(ctx, PWA_E_STATE, "MC sample is empty: no normalisation");
     pwa_status st;
-    if (need_mc && (st = ensure_gram(ctx)) != PWA_OK) return st;
+    if (need_mc && !ctx->gram_valid && (st = refuse_capture(ctx, "MC matrix")) != PWA_OK) return st;
     const int blocks = hessian_blocks(ctx->prec, k, ctx->cu_count, nd);
     const size_t n_work = hessian_work_doubles(k, blocks), n_h = 4 * (size_t)k * k + 1;
     const size_t doubles = n_work + 1;                  // the work buffer, then the status word and arrival count
@@ -1090,6 +1101,7 @@ pwa_status pwa_hessian(pwa_ctx *ctx, const double *V, double *H) {
             return hip_fail(ctx, he, "hipHostMalloc(hessian output)");
         }
     }
+    if (need_mc && (st = ensure_gram(ctx)) != PWA_OK) return st;
     double *work = static_cast<double *>(ctx->h_buf);
     unsigned *flag = reinterpret_cast<unsigned *>(work + n_work);
     // without MC rows (Eq. 2 form, no data) there is no normalisation term
@@ -1162,7 +1174,7 @@ pwa_status pwa_autotune(pwa_ctx *ctx, int32_t reps, pwa_stream_cfg *best, double
     ctx->timing = false;
     StreamArgs a;
     int blocks = 0;
-    pwa_status st = prepare(ctx, a, &blocks);
+    pwa_status st = prepare(ctx, nullptr, a, &blocks);
     if (st != PWA_OK) return st;
     for (int i = 0; i < ctx->k; ++i) {      // any nonzero V: only the time matters
         a.v_arg[2 * i] = 1.0 / (1.0 + i);
